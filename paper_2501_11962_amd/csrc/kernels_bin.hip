@@ -175,7 +175,7 @@ __global__ void __launch_bounds__(EWB) k_bin_place(const SegDev* __restrict__ se
     wsp<int>(ws, sg.o_slotof)[(size_t)b * Q + i] = slot;
 }
 
-// Padding slots of each column: position of the column's last atom, DUMMY_KEY.
+// Padding slots of each column: position of the column's last atom, PAD_W, DUMMY_KEY.
 __global__ void __launch_bounds__(EWB) k_bin_pad(const SegDev* __restrict__ segs, Launch L, char* ws) {
     const int blk = blockIdx.x;
     const int p = find_seg(L, blk);
@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(EWB) k_bin_pad(const SegDev* __restrict__ segs
     int* og = wsp<int>(ws, sg.o_orig) + (size_t)b * S;
     const uint4 last = up[base + n - 1];
     for (int k = n; k < pad; ++k) {
-        up[base + k] = last;
+        up[base + k] = make_uint4(last.x, last.y, last.z, PAD_W);
         um[base + k] = make_int2(DUMMY_KEY, 0);
         og[base + k] = -1;
     }

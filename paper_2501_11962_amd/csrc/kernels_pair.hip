@@ -8,17 +8,27 @@
 //      within the search radius of the cluster's bounding box, and per column the
 //      cluster range covering the z window [zlo - r, zhi + r] (two ranges when the
 //      window wraps around the box).
-//   2. Candidate clusters are listed in LDS; 8 of them (64 atoms) are loaded per step,
-//      one atom per lane, converted to FP32 coordinates relative to the i-cluster's box
-//      centre (exact integer minimum image, then one rounding) and kept when within the
-//      cutoff of the i-cluster's bounding box.  Survivors are compacted (ballot + mbcnt)
-//      into a per-wave LDS ring.
-//   3. Every EB (64) ring entries, EB/8 steps of 8 j-atoms x 8 i-atoms (lane = 8*i + j)
+//   2. Candidate clusters are listed in LDS; the positions of 8 of them (64 atoms) are
+//      loaded per step, one atom per lane, converted to FP32 coordinates relative to the
+//      i-cluster's box centre (exact integer minimum image, then one rounding) and tested
+//      against the search radius around the i-cluster's bounding box.  The slots of the
+//      survivors are compacted (ballot + mbcnt) into a per-wave LDS list.
+//   3. Every 64 listed slots: the atoms are gathered, one per lane, converted and written
+//      to a 64-entry LDS ring, and 8 steps of 8 j-atoms x 8 i-atoms (lane = 8*i + j)
 //      evaluate the pair terms; each lane accumulates a partial sum for its i atom.
 //   4. Partial sums are reduced over the 8 j lanes.
 //   The force pass records each cluster's neighbour list (one record per candidate
 //   cluster with survivors); the Hessian pass of the same bead replays it instead of
-//   steps 1-2.
+//   steps 1-2: the records' atom masks give the slot list directly.
+//   What bounds the kernels is the issue time of vector instructions (LDS and memory have
+//   slack), and on gfx950 their rates differ: FP32 add, multiply and fma, 32-bit integer
+//   add and bitwise operations on vector registers take 2 cycles per wave and SIMD; the
+//   same with a scalar-register operand, and compares, conversions, shifts, min / max,
+//   three-operand integer operations, DPP forms and v_mbcnt 4; rsq, rcp and exp 8 (timed
+//   in loops of independent instructions, 8 waves per SIMD).  Only survivors are therefore
+//   converted, charged and written to the ring, all 64 lanes at work: of the candidates
+//   tested, and of the atoms of recorded clusters, only about 58% survive (150,000-atom
+//   workload), and the ring writes and conversions of the idle lanes cost as much.
 // Launch: a flat grid (one workgroup per W clusters, k_pair) or, as a plan option, a
 // persistent grid over per-XCD work queues (k_pair_q); both run the same per-wave body.
 // Energies are a template parameter, so that kernels that need none take fewer
@@ -64,21 +74,17 @@
 
 namespace mop {
 
-// Ring entries evaluated per batch (EB / 8 steps of 8 j-atoms), as soon as that many wait.
-// Each lane sums its entries in ring order, so the batch size changes no result; measured
-// on the membrane workload, batches of 32 and 16 were 2% and 8% slower than 64 (the fixed
-// cost of a batch outweighs the better spread of pair work between candidate loads).
-#ifndef MOP_EVAL_BATCH
-#define MOP_EVAL_BATCH 64
-#endif
-constexpr int EB = MOP_EVAL_BATCH;
-static_assert(EB % 8 == 0 && EB <= 64 && RING % EB == 0, "evaluation batch");
+// Ring entries evaluated per batch: one per lane of the wave that gathers them.
+constexpr int EB = RING;
+static_assert(EB == 64, "evaluation batch");
 
 // Ring of j-atoms, one per wave in LDS (ints stored as float bits; the key word is the
 // packed 16 * exclusion key + LJ type of the system's key table).  Full-shell kernels keep
 // entries as float4 {x, y, z, q} followed by float4 {key, v_x, v_y, v_z} (Hessian) or a
 // float {key} (force), so a step reads a j-atom with one or two 16-byte loads.  The
 // Newton-3 kernels keep one array per field [field][entry], F_* below.
+typedef float v4f __attribute__((ext_vector_type(4)));
+
 constexpr int F_X = 0, F_Y = 1, F_Z = 2, F_Q = 3, F_K = 4, F_S = 5, F_J = 6;
 
 // Table entries per type pair in LDS, 16 bytes apart: the force kernels keep
@@ -87,8 +93,8 @@ constexpr int F_X = 0, F_Y = 1, F_Z = 2, F_Q = 3, F_K = 4, F_S = 5, F_J = 6;
 template <int MODE>
 constexpr int TAB_COPIES = MODE == 1 ? 1 : 2;
 
-// erfc(x) for 0 <= x <= 6 given ex2 = exp(-x^2).
-__device__ __forceinline__ float erfc_ex2(float x, float ex2) {
+// erfcx(x) = exp(x^2) erfc(x) for 0 <= x <= 6.
+__device__ __forceinline__ float erfcx_poly(float x) {
     const float t = __builtin_amdgcn_rcpf(fmaf(0.5f, x, 1.0f));
     float p = -3.256256573e-02f;
     p = fmaf(p, t, 2.505454269e-01f);
@@ -99,8 +105,14 @@ __device__ __forceinline__ float erfc_ex2(float x, float ex2) {
     p = fmaf(p, t, 2.504345553e-01f);
     p = fmaf(p, t, 2.859732478e-01f);
     p = fmaf(p, t, -2.038257043e-04f);
-    return ex2 * p;
+    return p;
 }
+
+// 32-bit words of LDS per wave: ring, candidate clusters (16 more, so that chunks can be
+// read whole and ahead), slots of survivors, survivor masks of 64 candidate clusters.
+constexpr int SLOTS = 128;  // power of two, at least 63 + 64
+template <int NF>
+constexpr int WAVE_LDS = NF * RING + (CLIST + 16) + SLOTS + 16;
 
 template <int MODE, int N3>
 struct Fields {
@@ -109,8 +121,8 @@ struct Fields {
 };
 
 struct IAtom {
-    float x, y, z, q, vx, vy, vz;
-    uint32_t ux, uy, uz;
+    float x, y, z;  // relative to the box centre, or (EX) raw fixed-point bits
+    float q, vx, vy, vz;
     uint32_t kp;  // 16 * (key + 2) + 15, from the packed word 16 * key + type
     int tiN;
     bool v;
@@ -131,6 +143,12 @@ constexpr bool THREE_Q = MODE == 1 && N3 == 0 && EL == 0;
 // HVP: g (v_i - v_j) + h (d . (v_i - v_j)) d) is added to (ax, ay, az) with fused
 // multiply-adds; with T_OUT it is also returned in t (for the j side).  tabrow points
 // at the type-table row of atom i.
+// Everything after the cutoff test runs only in the lanes of pairs that interact (58% on
+// the 150,000-atom workload): no selects on the results, and the idle lanes draw no
+// power, which the kernels are short of (they run at 1.8-2.1 GHz of the GPU's 2.4).
+// Every fused multiply-add is written out (contraction is off), so that the variants of
+// the kernels agree bit for bit.
+// round3: r^-3 is rounded before it is taken from 2 k_rf (force, reaction field).
 template <int MODE, bool EX, bool WANTE, bool T_OUT, int EL, bool Q3 = false>
 __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const float4* tabrow,
                                           int ntab,
@@ -138,12 +156,13 @@ __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const 
                                           float qj, uint32_t kj, float vjx, float vjy,
                                           float vjz, bool valid, float& ax, float& ay,
                                           float& az, float& tx, float& ty, float& tz,
-                                          float& en) {
+                                          float& en, bool round3 = false) {
+#pragma clang fp contract(off)
     float dx, dy, dz;
     if (EX) {
-        dx = (float)(int)(__float_as_uint(jx) - I.ux) * P.sx;
-        dy = (float)(int)(__float_as_uint(jy) - I.uy) * P.sy;
-        dz = (float)(int)(__float_as_uint(jz) - I.uz) * P.sz;
+        dx = (float)(int)(__float_as_uint(jx) - __float_as_uint(I.x)) * P.sx;
+        dy = (float)(int)(__float_as_uint(jy) - __float_as_uint(I.y)) * P.sy;
+        dz = (float)(int)(__float_as_uint(jz) - __float_as_uint(I.z)) * P.sz;
     } else {
         dx = jx - I.x;
         dy = jy - I.y;
@@ -156,90 +175,88 @@ __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const 
     const uint32_t kd = I.kp - kj;
     const int tj = (int)(kj & 15u);
     const bool exc = kd <= 79u;
-    const bool near = valid & I.v & (r2 < P.rc2);
-    const bool in = near & !exc;
-    const bool cor = EL == 1 && near && exc && (kd - 32u > 15u);  // Ewald correction
-    // masked lanes (self pair at r = 0, stale ring entries) may form inf/NaN here; every
-    // result they feed is replaced by 0 through a select below, never multiplied
-    const float r2s = r2;
-    const float rinv = __builtin_amdgcn_rsqf(r2s);
-    const float rinv2 = rinv * rinv;
-    const float rinv3 = rinv2 * rinv;
-    const float rinv6 = rinv3 * rinv3;
-    const float4 T = tabrow[tj];
-    const float qq = I.q * qj;  // 3 q_i q_j when Q3
-    const float C1 = fmaf(qq, Q3 ? P.crf1_3 : P.crf1, T.z);
-    const float G6 = fmaf(T.x, rinv6, T.y);
-    const float rinv8 = rinv6 * rinv2;
-    float g, E = 0.0f, D = 0.0f, r = 0.0f;
-    if (EL == 0) {
-        g = G6 * rinv8;
-        g = fmaf(qq, Q3 ? fmaf(rinv3, -1.0f / 3.0f, P.krf2_3) : P.krf2 - rinv3, g);
-        g = fmaf(C1, rinv, g);
-        g = in ? g : 0.0f;
-    } else {
-        r = r2s * rinv;
-        const float bx = P.beta * r;
-        const float ex2 = __expf(-bx * bx);
-        const float ec = erfc_ex2(bx, ex2);
-        D = P.c2b * ex2;
-        E = exc ? ec - 1.0f : ec;
-        const float ge = -fmaf(D, rinv2, E * rinv3);
-        const float gs = fmaf(G6, rinv8, C1 * rinv);
-        g = in ? fmaf(qq, ge, gs) : (cor ? qq * ge : 0.0f);
-    }
-    if (MODE == 0) {
-        if (T_OUT) {
-            tx = g * dx;
-            ty = g * dy;
-            tz = g * dz;
-            ax += tx;
-            ay += ty;
-            az += tz;
-        } else {
-            ax = fmaf(g, dx, ax);
-            ay = fmaf(g, dy, ay);
-            az = fmaf(g, dz, az);
-        }
-        if (WANTE) {
-            const float4 T2 = tabrow[ntab + tj];
-            if (EL == 0) r = r2s * rinv;
-            float e = fmaf(T2.z, rinv6, -T2.w) * rinv6;
-            const float eel = EL == 0 ? rinv + P.krf * r2s - P.crf + P.e0rf + P.crf1 * r
-                                      : fmaf(E, rinv, fmaf(P.crf1, r, P.e0rf));
-            e = fmaf(qq, eel, e);
-            e += fmaf(T.z, r, T.w);
-            en = in ? e : (cor ? qq * E * rinv : 0.0f);
-        }
-    } else {
-        const float h6 = fmaf(T.w, rinv6, G6);
-        float h;
+    // Ewald: excluded partners carry a correction, the atom itself nothing
+    const bool act = EL == 1 ? kd - 32u > 15u : !exc;
+    if (T_OUT) tx = ty = tz = 0.0f;
+    if (valid & I.v & act & (r2 < P.rc2)) {
+        const float rinv = __builtin_amdgcn_rsqf(r2);
+        const float rinv2 = rinv * rinv;
+        const float rinv3 = rinv2 * rinv;
+        const float rinv6 = rinv3 * rinv3;
+        const float4 T = tabrow[tj];
+        const float qq = I.q * qj;  // 3 q_i q_j when Q3
+        const float C1 = fmaf(qq, Q3 ? P.crf1_3 : P.crf1, T.z);
+        const float G6 = fmaf(T.x, rinv6, T.y);
+        const float rinv8 = rinv6 * rinv2;
+        float g, E = 0.0f, D = 0.0f, r = 0.0f;
         if (EL == 0) {
-            // h = r^-5 (3 qq - 8 h6 r^-5) - C1 r^-3
-            const float rinv5 = rinv3 * rinv2;
-            h = fmaf(h6 * rinv5, -8.0f, Q3 ? qq : 3.0f * qq);
-            h = fmaf(rinv5, h, -(C1 * rinv3));
-            h = in ? h : 0.0f;
+            g = G6 * rinv8;
+            g = fmaf(qq, Q3 ? fmaf(rinv3, -1.0f / 3.0f, P.krf2_3)
+                            : (round3 ? P.krf2 - rinv3 : fmaf(-rinv, rinv2, P.krf2)), g);
+            g = fmaf(C1, rinv, g);
         } else {
-            h = h6 * (rinv8 * (-8.0f * rinv2));
-            const float he = fmaf(P.b2x2, D, 3.0f * fmaf(D, rinv2, E * rinv3)) * rinv2;
-            h = fmaf(-C1, rinv3, h);
-            h = in ? fmaf(qq, he, h) : (cor ? qq * he : 0.0f);
+            r = r2 * rinv;
+            const float bx = P.beta * r;
+            const float ex2 = __expf(-bx * bx);
+            const float ecx = erfcx_poly(bx);
+            D = P.c2b * ex2;
+            E = exc ? fmaf(ex2, ecx, -1.0f) : ex2 * ecx;
+            const float ge = -fmaf(D, rinv2, E * rinv3);
+            const float gs = fmaf(G6, rinv8, C1 * rinv);
+            g = exc ? qq * ge : fmaf(qq, ge, gs);
         }
-        const float dvx = I.vx - vjx, dvy = I.vy - vjy, dvz = I.vz - vjz;
-        const float sd = fmaf(dx, dvx, fmaf(dy, dvy, dz * dvz));
-        const float hs = h * sd;
-        if (T_OUT) {
-            tx = fmaf(g, dvx, hs * dx);
-            ty = fmaf(g, dvy, hs * dy);
-            tz = fmaf(g, dvz, hs * dz);
-            ax += tx;
-            ay += ty;
-            az += tz;
+        if (MODE == 0) {
+            if (T_OUT) {
+                tx = g * dx;
+                ty = g * dy;
+                tz = g * dz;
+                ax += tx;
+                ay += ty;
+                az += tz;
+            } else {
+                ax = fmaf(g, dx, ax);
+                ay = fmaf(g, dy, ay);
+                az = fmaf(g, dz, az);
+            }
+            if (WANTE) {
+                const float4 T2 = tabrow[ntab + tj];
+                if (EL == 0) r = r2 * rinv;
+                float e = fmaf(T2.z, rinv6, -T2.w) * rinv6;
+                const float eel = EL == 0 ? fmaf(P.crf1, r, (fmaf(P.krf, r2, rinv) - P.crf) + P.e0rf)
+                                          : fmaf(E, rinv, fmaf(P.crf1, r, P.e0rf));
+                e = fmaf(qq, eel, e);
+                e += fmaf(T.z, r, T.w);
+                en = EL == 1 && exc ? qq * E * rinv : e;
+            }
         } else {
-            ax = fmaf(g, dvx, fmaf(hs, dx, ax));
-            ay = fmaf(g, dvy, fmaf(hs, dy, ay));
-            az = fmaf(g, dvz, fmaf(hs, dz, az));
+            const float h6 = fmaf(T.w, rinv6, G6);
+            float h;
+            if (EL == 0) {
+                // h = r^-5 (3 qq - 8 h6 r^-5) - C1 r^-3
+                const float rinv5 = rinv3 * rinv2;
+                h = fmaf(h6 * rinv5, -8.0f, Q3 ? qq : 3.0f * qq);
+                h = fmaf(rinv5, h, -(C1 * rinv3));
+            } else {
+                h = h6 * (rinv8 * (-8.0f * rinv2));
+                const float he = fmaf(P.b2x2, D, 3.0f * fmaf(D, rinv2, E * rinv3)) * rinv2;
+                h = fmaf(-C1, rinv3, h);
+                h = exc ? qq * he : fmaf(qq, he, h);
+            }
+            const float dvx = I.vx - vjx, dvy = I.vy - vjy, dvz = I.vz - vjz;
+            const float sd = fmaf(dx, dvx, fmaf(dy, dvy, dz * dvz));
+            const float hs = h * sd;
+            if (T_OUT) {
+                tx = fmaf(g, dvx, hs * dx);
+                ty = fmaf(g, dvy, hs * dy);
+                tz = fmaf(g, dvz, hs * dz);
+                ax += tx;
+                ay += ty;
+                az += tz;
+            } else {
+                ax = fmaf(g, dvx, fmaf(hs, dx, ax));
+                ay = fmaf(g, dvy, fmaf(hs, dy, ay));
+                az = fmaf(g, dvz, fmaf(hs, dz, az));
+            }
         }
     }
 }
@@ -259,16 +276,19 @@ __device__ __forceinline__ void load_table(const SegDev* __restrict__ sg, float4
 }
 
 // The work of one wave: i-cluster gw of path p (bead bead0 + gw / cpb, cluster gw % cpb),
-// with the path's table at s_tab and the wave's own ring and candidate list in LDS.
+// with the path's table at s_tab and the wave's own WAVE_LDS words of LDS at ring.
 // ENERGY: the kernel can sum pair energies (of bead energy_bead, or of every bead for -2);
 // kernels without it need fewer registers.
 template <int MODE, int N3, int EL, int ENERGY>
 __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const Launch& L,
                                           char* __restrict__ ws, int outsel, int energy_bead,
                                           int lists, int bead0, int p, int gw, const float4* s_tab,
-                                          float* ring, int* clist) {
+                                          float* ring) {
     using FL = Fields<MODE, N3>;
     constexpr int NF = FL::NF, FV = FL::V;
+    int* clist = reinterpret_cast<int*>(ring) + NF * RING;
+    int* slist = clist + CLIST + 16;
+    unsigned long long* smask = reinterpret_cast<unsigned long long*>(slist + SLOTS);
     const SegDev* __restrict__ sg = segs + p;
     const int nt = sg->s.nt;
     const int lane = threadIdx.x & 63;
@@ -305,6 +325,8 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
     P.b2x2 = sg->s.ew_b2x2;
     P.krf2_3 = sg->s.krf2 * (1.0f / 3.0f);
     P.crf1_3 = sg->s.crf1 * (1.0f / 3.0f);
+    // a scalar operand would halve the rate of the instructions that read it
+    if (MODE == 0) asm("" : "+v"(P.krf2), "+v"(P.crf1));
     constexpr float QSC = THREE_Q<MODE, N3, EL> ? 3.0f : 1.0f;
     const float sx = P.sx, sy = P.sy, sz = P.sz;
     const float rcs = sg->s.rcs, rcs2 = sg->s.rcs2;
@@ -324,9 +346,6 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
     I.tiN = mi.y * nt;
     const float4* tabrow = s_tab + I.tiN;
     const int ntab = nt * nt;
-    I.ux = ui.x;
-    I.uy = ui.y;
-    I.uz = ui.z;
     I.vx = I.vy = I.vz = 0.0f;
     if (MODE == 1) {
         const float4 v4 = vs[si];
@@ -375,55 +394,29 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
         loz -= fz;
         hiz -= fz;
     }
-    I.x = (float)(int)(ui.x - ucx) * sx;
-    I.y = (float)(int)(ui.y - ucy) * sy;
-    I.z = (float)(int)(ui.z - ucz) * sz;
     // Coordinates relative to the reference give exact pair differences when
     // max(|lo|, |hi|) + search radius < L/2 along every axis: for a pair within the
     // cutoff, (image of i) + d then lies within L/2 of the reference, so it is the image
     // of j that the relative coordinate picks.  Otherwise each pair difference is taken
     // from the fixed-point coordinates (small boxes, sparse columns).
-    const bool exact = (fmaxf(-lox, hix) + rcs >= 0.5f * sg->s.Lf[0]) ||
+    const bool exact_l = (fmaxf(-lox, hix) + rcs >= 0.5f * sg->s.Lf[0]) ||
                        (fmaxf(-loy, hiy) + rcs >= 0.5f * sg->s.Lf[1]) ||
                        (fmaxf(-loz, hiz) + rcs >= 0.5f * sg->s.Lf[2]);
-    const int cx = fixed_bin(ref.x, ncx), cy = fixed_bin(ref.y, ncy);
-
-    // z window of candidate atoms of a column whose rectangle is (gx, gy) away from the
-    // bounding box: |z - box| < sqrt(rcs^2 - gx^2 - gy^2), in z bins (per lane)
-    const float Lz = sg->s.Lf[2];
-    // reciprocals instead of divisions: a z bound off by one fixed-point unit, or a
-    // column image chosen either way at an exact half-box tie (both images then lie at
-    // the same distance), changes no test
-    const float isz = 1.0f / sz;
-    auto zwindow = [&](float g2, bool& fullz, bool& zwrap, int& zb0, int& zb1)
-                       __attribute__((always_inline)) {
-        const float hz = sqrtf(fmaxf(rcs2 - g2, 0.0f));
-        fullz = (hiz - loz + 2.0f * hz) >= Lz;
-        zb0 = 0;
-        zb1 = nzb - 1;
-        zwrap = false;
-        if (!fullz) {
-            const long long dlo = (long long)floorf((loz - hz) * isz);
-            const long long dhi = (long long)ceilf((hiz + hz) * isz);
-            const uint32_t zlo = ucz + (uint32_t)dlo;
-            const uint32_t zhi = ucz + (uint32_t)dhi;
-            zb0 = fixed_bin(zlo, nzb);
-            zb1 = fixed_bin(zhi, nzb);
-            zwrap = zlo > zhi;
-            if (zwrap && zb1 + 1 >= zb0) fullz = true;
-        }
-    };
-    const float bcx = 0.5f * (lox + hix), bhx = 0.5f * (hix - lox);
-    const float bcy = 0.5f * (loy + hiy), bhy = 0.5f * (hiy - loy);
-    const float xref = (float)ucx * sx, yref = (float)ucy * sy;
-    const float Lx = sg->s.Lf[0], Ly = sg->s.Lf[1];
-    const float iLx = 1.0f / Lx, iLy = 1.0f / Ly;
-    const float cwx = sg->s.cw[0], cwy = sg->s.cw[1];
+    const bool exact = __builtin_amdgcn_readfirstlane((int)exact_l) != 0;  // uniform
+    if (exact) {
+        I.x = __uint_as_float(ui.x);
+        I.y = __uint_as_float(ui.y);
+        I.z = __uint_as_float(ui.z);
+    } else {
+        I.x = (float)(int)(ui.x - ucx) * sx;
+        I.y = (float)(int)(ui.y - ucy) * sy;
+        I.z = (float)(int)(ui.z - ucz) * sz;
+    }
 
     float ax = 0.f, ay = 0.f, az = 0.f;
     float eacc = 0.0f;
     double eacc64 = 0.0;
-    int wp = 0, rp = 0;  // ring write / read counters (uniform); rp stays a multiple of EB
+    int wp = 0, rp = 0;  // slots listed / gathered (uniform); rp stays a multiple of 64
     int wr = 0;          // neighbour-list records written (force pass)
 
     float4* ring4 = reinterpret_cast<float4*>(ring);
@@ -482,13 +475,11 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
         eacc += 0.5f * en;
     }
 
-    // ---- 8 j-atoms x 8 i-atoms per step from ring entries [base, base + count) ------
-    // base is a multiple of EB, so reads of a chunk never wrap and every field of every
-    // step is one immediate offset from the same address.
-    auto eval_t = [&]<bool EX, bool WE, bool FULL>(int base, int count)
-                      __attribute__((always_inline)) {
-        float* rb = ring + (base & (RING - 1)) + jslot;
-        const int e0 = (base & (RING - 1)) + jslot;
+    // ---- 8 j-atoms x 8 i-atoms per step from ring entries [0, count) ----------------
+    // Every field of every step is one immediate offset from the same address.  Entries
+    // past the count of a partial batch are zero.
+    auto eval_t = [&]<bool EX, bool WE, bool FULL>(int count) __attribute__((always_inline)) {
+        float* rb = ring + jslot;
         const int nsteps = FULL ? EB / 8 : (count + 7) >> 3;
 #pragma unroll
         for (int s = 0; s < nsteps; ++s) {
@@ -507,42 +498,30 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
                     vjz = rb[(FV + 2) * RING + o];
                 }
             } else {
-                const float4 a = ring4[e0 + o];
-                jx = a.x;
-                jy = a.y;
-                jz = a.z;
-                qj = a.w;
+                // the empty asm keeps the reads 16 bytes wide and here: their parts would
+                // otherwise sink into the masked region of pair_term as reads of their own
+                v4f a = *reinterpret_cast<const v4f*>(ring4 + o + jslot);
+                asm volatile("" : "+v"(a));
+                jx = a[0];
+                jy = a[1];
+                jz = a[2];
+                qj = a[3];
                 if (MODE == 1) {
-                    const float4 w = ring4[RING + e0 + o];
-                    kj = __float_as_uint(w.x);
-                    vjx = w.y;
-                    vjy = w.z;
-                    vjz = w.w;
+                    v4f w = *reinterpret_cast<const v4f*>(ring4 + RING + o + jslot);
+                    asm volatile("" : "+v"(w));
+                    kj = __float_as_uint(w[0]);
+                    vjx = w[1];
+                    vjy = w[2];
+                    vjz = w[3];
                 } else {
-                    kj = __float_as_uint(ring[4 * RING + e0 + o]);
+                    kj = __float_as_uint(ring[4 * RING + o + jslot]);
                 }
             }
             const bool valid = FULL || o + jslot < count;
-            // Entries past the count of a partial chunk may hold anything (never written
-            // in this wave's lifetime): masked products are still formed (0 * dx, 0 * dv),
-            // so give them finite operands and a valid table index.
-            float jxv = jx, jyv = jy, jzv = jz, qjv = qj;
-            uint32_t kjv = kj;
-            if (!FULL) {
-                jxv = valid ? jx : 0.0f;
-                jyv = valid ? jy : 0.0f;
-                jzv = valid ? jz : 0.0f;
-                qjv = valid ? qj : 0.0f;
-                kjv = valid ? kj : 0u;
-                if (MODE == 1) {
-                    vjx = valid ? vjx : 0.0f;
-                    vjy = valid ? vjy : 0.0f;
-                    vjz = valid ? vjz : 0.0f;
-                }
-            }
             float tx, ty, tz, en = 0.f;
-            pair_term<MODE, EX, WE, N3 == 1, EL, THREE_Q<MODE, N3, EL>>(I, P, tabrow, ntab, jxv, jyv, jzv, qjv, kjv, vjx, vjy,
-                                             vjz, valid, ax, ay, az, tx, ty, tz, en);
+            pair_term<MODE, EX, WE, N3 == 1, EL, THREE_Q<MODE, N3, EL>>(I, P, tabrow, ntab, jx, jy, jz, qj, kj, vjx, vjy,
+                                             vjz, valid, ax, ay, az, tx, ty, tz, en,
+                                             ENERGY && FULL && s == 0);
             if (WE) eacc += N3 ? en : 0.5f * en;
             if (N3) {
                 // sum the j side over the 8 i lanes (lanes 8 apart), then the 8 lanes of
@@ -571,194 +550,193 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
             // j-side sums of this chunk (stored with the sign of the i side) go to the
             // slot-order buffer, one entry per lane
             wave_sync();
-            if (FULL ? lane < EB : lane < count) {
-                const int e = (base & (RING - 1)) + lane;
-                const int slot = __float_as_int(ring[F_S * RING + e]);
-                unsafeAtomicAdd(fsx + slot, -ring[(F_J + 0) * RING + e]);
-                unsafeAtomicAdd(fsy + slot, -ring[(F_J + 1) * RING + e]);
-                unsafeAtomicAdd(fsz + slot, -ring[(F_J + 2) * RING + e]);
+            if (FULL || lane < count) {
+                const int slot = __float_as_int(ring[F_S * RING + lane]);
+                unsafeAtomicAdd(fsx + slot, -ring[(F_J + 0) * RING + lane]);
+                unsafeAtomicAdd(fsy + slot, -ring[(F_J + 1) * RING + lane]);
+                unsafeAtomicAdd(fsz + slot, -ring[(F_J + 2) * RING + lane]);
             }
         }
     };
-    auto eval = [&]<bool FULL>(int base, int count) __attribute__((always_inline)) {
+    auto eval = [&]<bool FULL>(int count) __attribute__((always_inline)) {
         if (exact) {
-            if (wantE) eval_t.template operator()<true, true, FULL>(base, count);
-            else eval_t.template operator()<true, false, FULL>(base, count);
+            if (wantE) eval_t.template operator()<true, true, FULL>(count);
+            else eval_t.template operator()<true, false, FULL>(count);
         } else {
-            if (wantE) eval_t.template operator()<false, true, FULL>(base, count);
-            else eval_t.template operator()<false, false, FULL>(base, count);
+            if (wantE) eval_t.template operator()<false, true, FULL>(count);
+            else eval_t.template operator()<false, false, FULL>(count);
         }
     };
 
-    // ---- candidate clusters [0, T) of clist --------------------------------------
-    // Candidate atoms are loaded one chunk (8 clusters) ahead of their use, so the
-    // global-load latency of chunk q+1 overlaps the tests, ring writes and pair
-    // evaluations of chunk q.
-    auto process = [&](int T) __attribute__((always_inline)) {
-        // lanes without a candidate load slot 0 (always present) and are rejected by
-        // the slot test below; no select between pointers, so the loads stay global
-        int nslot = (lane >> 3) < T ? clist[lane >> 3] * CLUSTER + (lane & 7) : -1;
-        uint4 nuj = upos[max(nslot, 0)];
-        int2 nmj = umeta[max(nslot, 0)];
-        float4 njv = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (MODE == 1) njv = vs[max(nslot, 0)];
-        for (int q = 0; q < T; q += 8) {
-            const int slot = nslot;
-            const uint4 uj = nuj;
-            const int2 mj = nmj;
-            const float4 jv = njv;
-            {
-                const int cn = q + 8 + (lane >> 3);
-                nslot = cn < T ? clist[cn] * CLUSTER + (lane & 7) : -1;
-                if (nslot >= 0) {
-                    nuj = upos[nslot];
-                    nmj = umeta[nslot];
-                    if (MODE == 1) njv = vs[nslot];
-                }
+    // ---- the batch of listed slots in flight ----------------------------------------
+    // gather() starts the loads of the next n (<= 64) listed atoms, one per lane;
+    // to_ring() converts them and writes them to the ring.
+    int gs = 0, gk = 0;
+    uint4 gu = make_uint4(0u, 0u, 0u, 0u);
+    float4 gv = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto gather = [&](int n) __attribute__((always_inline)) {
+        const int sl = slist[(rp & (SLOTS - 1)) + lane];
+        gs = lane < n ? sl : 0;  // lanes past the list load slot 0 (always present)
+        gu = upos[(uint32_t)gs];
+        if (MODE == 1) gv = vs[(uint32_t)gs];  // .w: the packed key
+        else gk = umeta[(uint32_t)gs].x;
+    };
+    auto to_ring = [&](int n) __attribute__((always_inline)) {
+        float jx, jy, jz;
+        if (exact) {
+            jx = __uint_as_float(gu.x);
+            jy = __uint_as_float(gu.y);
+            jz = __uint_as_float(gu.z);
+        } else {
+            jx = (float)(int)(gu.x - ucx) * sx;
+            jy = (float)(int)(gu.y - ucy) * sy;
+            jz = (float)(int)(gu.z - ucz) * sz;
+        }
+        float jq = QSC * __uint_as_float(gu.w);
+        float jk = MODE == 1 ? gv.w : __int_as_float(gk);
+        float vx = gv.x, vy = gv.y, vz = gv.z;
+        if (n < 64) {
+            const bool v = lane < n;
+            jx = v ? jx : 0.0f;
+            jy = v ? jy : 0.0f;
+            jz = v ? jz : 0.0f;
+            jq = v ? jq : 0.0f;
+            jk = v ? jk : 0.0f;
+            vx = v ? vx : 0.0f;
+            vy = v ? vy : 0.0f;
+            vz = v ? vz : 0.0f;
+        }
+        if (N3) {
+            float* re = ring + lane;
+            re[F_X * RING] = jx;
+            re[F_Y * RING] = jy;
+            re[F_Z * RING] = jz;
+            re[F_Q * RING] = jq;
+            re[F_K * RING] = jk;
+            re[F_S * RING] = __int_as_float(gs);
+            re[(F_J + 0) * RING] = 0.0f;
+            re[(F_J + 1) * RING] = 0.0f;
+            re[(F_J + 2) * RING] = 0.0f;
+            if (MODE == 1) {
+                re[FV * RING] = vx;
+                re[(FV + 1) * RING] = vy;
+                re[(FV + 2) * RING] = vz;
             }
-            float jx = (float)(int)(uj.x - ucx) * sx;
-            float jy = (float)(int)(uj.y - ucy) * sy;
-            float jz = (float)(int)(uj.z - ucz) * sz;
-            const float ex = fmaxf(fmaxf(lox - jx, jx - hix), 0.0f);
-            const float ey = fmaxf(fmaxf(loy - jy, jy - hiy), 0.0f);
-            const float ez = fmaxf(fmaxf(loz - jz, jz - hiz), 0.0f);
-            const bool pass = (slot >= 0) & (mj.x != DUMMY_KEY) &
-                              (fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < rcs2);
-            if (exact) {
-                jx = __uint_as_float(uj.x);
-                jy = __uint_as_float(uj.y);
-                jz = __uint_as_float(uj.z);
-            }
-            const float jq = __uint_as_float(uj.w);
-            const int jk = mj.x;
-            const unsigned long long m = __ballot(pass);
-            const int off = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-            wave_sync();  // previous reads of the ring are done before it is overwritten
-            if (rec) {
-                // one record per candidate cluster of this chunk with a survivor, in
-                // candidate order: (cluster index << 8) | mask of its surviving atoms.
-                // Lanes 8k .. 8k+7 hold the atoms of the chunk's k-th cluster; lane 8k
-                // writes its record (its slot is the cluster's first).
-                const uint32_t mk = (lane & 7) == 0 ? (uint32_t)(m >> lane) & 0xFFu : 0u;
-                const unsigned long long nzm = __ballot(mk != 0u);
-                if (mk != 0u) {
-                    const int pos = wr + __builtin_amdgcn_mbcnt_hi(
-                        (unsigned)(nzm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)nzm, 0u));
-                    if (pos < lcap) nl[pos] = (int)(((uint32_t)slot << 5) | mk);
-                }
-                wr += (int)__popcll(nzm);
-            }
-            if (pass) {
-                const int e = (wp + off) & (RING - 1);
-                if (N3) {
-                    float* re = ring + e;
-                    re[F_X * RING] = jx;
-                    re[F_Y * RING] = jy;
-                    re[F_Z * RING] = jz;
-                    re[F_Q * RING] = QSC * jq;
-                    re[F_K * RING] = __int_as_float(jk);
-                    re[F_S * RING] = __int_as_float(slot);
-                    re[(F_J + 0) * RING] = 0.0f;
-                    re[(F_J + 1) * RING] = 0.0f;
-                    re[(F_J + 2) * RING] = 0.0f;
-                    if (MODE == 1) {
-                        re[FV * RING] = jv.x;
-                        re[(FV + 1) * RING] = jv.y;
-                        re[(FV + 2) * RING] = jv.z;
-                    }
-                } else {
-                    ring4[e] = make_float4(jx, jy, jz, QSC * jq);
-                    if (MODE == 1) ring4[RING + e] = make_float4(__int_as_float(jk), jv.x, jv.y, jv.z);
-                    else ring[4 * RING + e] = __int_as_float(jk);
-                }
-            }
-            wp += __popcll(m);
-            wave_sync();
-            while (wp - rp >= EB) {
-                eval.template operator()<true>(rp, EB);
-                rp += EB;
-                wave_sync();
-            }
+        } else {
+            ring4[lane] = make_float4(jx, jy, jz, jq);
+            if (MODE == 1) ring4[RING + lane] = make_float4(jk, vx, vy, vz);
+            else ring[4 * RING + lane] = jk;
         }
     };
 
-    // ---- replay of a recorded list: 8 records (up to 64 atoms) per chunk -----------
-    // Lane l takes atom l & 7 of record l >> 3 and keeps it when the record's mask has its
-    // bit; survivors are compacted into the ring exactly as the search compacted them, so
-    // the ring order, and every sum, is the search's.  Records are read two chunks ahead,
-    // atom data one chunk ahead.
-    auto replay = [&](int cnt) __attribute__((always_inline)) {
-        const int rsub = lane >> 3, atom = lane & 7;
-        uint32_t r1 = rsub < cnt ? (uint32_t)nl[rsub] : 0u;
-        uint32_t r2 = 8 + rsub < cnt ? (uint32_t)nl[8 + rsub] : 0u;
-        bool p1 = (r1 >> atom) & 1u;
-        int s1 = (int)(r1 >> 8) * CLUSTER + atom;  // a lane without a record reads slot atom
-        uint4 nuj = make_uint4(0u, 0u, 0u, 0u);
-        int2 nmj = make_int2(0, 0);
-        float4 njv = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (p1) {
-            nuj = upos[s1];
-            nmj = umeta[s1];
-            if (MODE == 1) njv = vs[s1];
-        }
-        for (int k0 = 0; k0 < cnt; k0 += 8) {
-            const uint4 uj = nuj;
-            const int2 mj = nmj;
-            const float4 jv = njv;
-            const bool pass = p1;
-            r1 = r2;
-            p1 = (r1 >> atom) & 1u;
-            s1 = (int)(r1 >> 8) * CLUSTER + atom;
-            if (p1) {
-                nuj = upos[s1];
-                nmj = umeta[s1];
-                if (MODE == 1) njv = vs[s1];
-            }
-            r2 = k0 + 16 + rsub < cnt ? (uint32_t)nl[k0 + 16 + rsub] : 0u;
-            float jx, jy, jz;
-            if (exact) {
-                jx = __uint_as_float(uj.x);
-                jy = __uint_as_float(uj.y);
-                jz = __uint_as_float(uj.z);
-            } else {
-                jx = (float)(int)(uj.x - ucx) * sx;
-                jy = (float)(int)(uj.y - ucy) * sy;
-                jz = (float)(int)(uj.z - ucz) * sz;
-            }
-            const unsigned long long m = __ballot(pass);
-            const int off = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-            wave_sync();  // the previous reads of the ring are done before it is overwritten
-            if (!N3 && pass) {  // full-shell kernels only
-                const int e = (wp + off) & (RING - 1);
-                ring4[e] = make_float4(jx, jy, jz, QSC * __uint_as_float(uj.w));
-                if (MODE == 1) ring4[RING + e] = make_float4(__int_as_float(mj.x), jv.x, jv.y, jv.z);
-                else ring[4 * RING + e] = __int_as_float(mj.x);
-            }
-            wp += __popcll(m);
-            wave_sync();
-            while (wp - rp >= EB) {
-                eval.template operator()<true>(rp, EB);
-                rp += EB;
-                wave_sync();
-            }
-        }
+    // Appends the slots of the lanes in m to the list.
+    auto append = [&](unsigned long long m, int slot) __attribute__((always_inline)) {
+        const int pos = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)wp));
+        wave_sync();  // the gather's reads of the list come first
+        if (__builtin_amdgcn_inverse_ballot_w64(m)) slist[pos & (SLOTS - 1)] = slot;
+        wave_sync();
+        wp += (int)__popcll(m);
     };
+    // mask of the lanes 0 .. 8 n - 1 (n >= 1)
+    auto lanes8 = [](int n) __attribute__((always_inline)) {
+        return n >= 8 ? ~0ull : (1ull << (8 * n)) - 1ull;
+    };
+
+    const int sub = lane >> 3, atom = lane & 7;
+
+    // ---- 64 listed slots: gather them, evaluate the batch gathered before -------------
+    int cur = 0;  // entries of the batch in flight
+    auto batch = [&]() __attribute__((always_inline)) {
+        if (cur > 0) to_ring(64);
+        gather(64);
+        rp += 64;
+        wave_sync();
+        if (cur > 0) eval.template operator()<true>(64);
+        wave_sync();  // reads of the ring are done before it is overwritten
+        cur = 64;
+    };
+
+    // ---- replay of a recorded list: 64 records at a time through LDS, 8 (up to 64 atoms)
+    // per chunk.  Lane l takes atom l & 7 of record l >> 3 and keeps it when the record's
+    // mask has its bit: the slots are listed in the order the search listed them, so every
+    // sum is the search's.  The next 64 records are read ahead.
     bool searched = true;
     if (rpl) {
         const int cnt = *nlc;
         if (cnt <= lcap) {
-            replay(cnt);
             searched = false;
+            uint32_t nr = lane < cnt ? (uint32_t)nl[lane] : 0u;
+            for (int k0 = 0; k0 < cnt; k0 += 64) {
+                clist[lane] = (int)nr;
+                const int kn = k0 + 64 + lane;
+                nr = kn < cnt ? (uint32_t)nl[kn] : 0u;
+                wave_sync();
+                const int nc = min(64, cnt - k0);
+                for (int q = 0; q < nc; q += 8) {
+                    const uint32_t r = (uint32_t)clist[q + sub];
+                    append(__builtin_amdgcn_ballot_w64((r & (1u << atom)) != 0u), (int)((r >> 8) << 3) | atom);
+                    if (wp - rp >= 64) batch();
+                }
+                wave_sync();
+            }
         }
     }
 
-    // ---- column stencil, 64 columns per pass ---------------------------------------
+    // ---- search ---------------------------------------------------------------------
+    // State: clusters [tq, T) of clist still to test.
     const int wx = sg->s.wx, wy = sg->s.wy, nst = searched ? wx * wy : 0;
-    for (int k0 = 0; k0 < nst; k0 += 64) {
-        const int k = k0 + lane;
-        int a0 = 0, a1 = 0, b0 = 0, b1 = 0;
+    int k0 = 0, skip = 0, T = 0, tq = 0;
+    uint4 nu = make_uint4(0u, 0u, 0u, 0u);
+    int nslot = 0;
+    // Positions of the chunk of 8 candidate clusters at clist[q] (one chunk ahead of use).
+    auto load_chunk = [&](int q) __attribute__((always_inline)) {
+        nslot = (clist[q + sub] << 3) | atom;
+        nu = upos[(uint32_t)nslot];
+    };
+    // Cluster ranges [a0, a1) and [b0, b1) of stencil column k of this lane (empty past the
+    // stencil).  Everything derived from the box is computed here, on its own copy of the
+    // bounds: hoisted out of the search it would hold a dozen registers through it.
+    auto columns = [&](int k, int& a0, int& a1, int& b0, int& b1) __attribute__((always_inline)) {
+        a0 = a1 = b0 = b1 = 0;
+        float qlx = lox, qhx = hix, qly = loy, qhy = hiy, qlz = loz, qhz = hiz;
+        uint32_t qux = ucx, quy = ucy, quz = ucz;
+        asm volatile("" : "+v"(qlx), "+v"(qhx), "+v"(qly), "+v"(qhy), "+v"(qlz), "+v"(qhz));
+        asm volatile("" : "+v"(qux), "+v"(quy), "+v"(quz));
+        // z window of candidate atoms of a column whose rectangle is (gx, gy) away from the
+        // bounding box: |z - box| < sqrt(rcs^2 - gx^2 - gy^2), in z bins (per lane)
+        const float Lz = sg->s.Lf[2];
+        // reciprocals instead of divisions: a z bound off by one fixed-point unit, or a
+        // column image chosen either way at an exact half-box tie (both images then lie at
+        // the same distance), changes no test
+        const float isz = sg->s.isz;
+        auto zwindow = [&](float g2, bool& fullz, bool& zwrap, int& zb0, int& zb1)
+                           __attribute__((always_inline)) {
+            const float hz = sqrtf(fmaxf(rcs2 - g2, 0.0f));
+            fullz = (qhz - qlz + 2.0f * hz) >= Lz;
+            zb0 = 0;
+            zb1 = nzb - 1;
+            zwrap = false;
+            if (!fullz) {
+                const long long dlo = (long long)floorf((qlz - hz) * isz);
+                const long long dhi = (long long)ceilf((qhz + hz) * isz);
+                const uint32_t zlo = quz + (uint32_t)dlo;
+                const uint32_t zhi = quz + (uint32_t)dhi;
+                zb0 = fixed_bin(zlo, nzb);
+                zb1 = fixed_bin(zhi, nzb);
+                zwrap = zlo > zhi;
+                if (zwrap && zb1 + 1 >= zb0) fullz = true;
+            }
+        };
+        const float bcx = 0.5f * (qlx + qhx), bhx = 0.5f * (qhx - qlx);
+        const float bcy = 0.5f * (qly + qhy), bhy = 0.5f * (qhy - qly);
+        const float xref = (float)qux * sx, yref = (float)quy * sy;
+        const float Lx = sg->s.Lf[0], Ly = sg->s.Lf[1];
+        const float iLx = sg->s.iL[0], iLy = sg->s.iL[1];
+        const float cwx = sg->s.cw[0], cwy = sg->s.cw[1];
+        // the column of the i-cluster (its reference atom's; the whole cluster's)
+        const uint4 ref = upos[c * CLUSTER + 3];
+        const int cx = fixed_bin(ref.x, ncx), cy = fixed_bin(ref.y, ncy);
         if (k < nst) {
             const int ox = k / wy, oy = k - ox * wy;
             // stencil half widths are below the column counts (else the stencil spans
@@ -808,30 +786,96 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
                 }
             }
         }
-        // flatten the per-column cluster ranges into clist, CLIST at a time
-        for (;;) {
-            const int len = (a1 - a0) + (b1 - b0);
+    };
+    // Lists the next up to CLIST candidate clusters; false when there are none left.  The
+    // clusters of 64 columns that did not fit are listed by later calls, which find their
+    // ranges again (k0: first of the 64 columns, skip: their clusters listed so far).
+    auto refill = [&]() __attribute__((always_inline)) {
+        while (k0 < nst) {
+            int a0, a1, b0, b1;
+            columns(k0 + lane, a0, a1, b0, b1);
+            const int la = a1 - a0, len = la + (b1 - b0);
             const int incl = wave_incl_scan(len);
             const int total = __builtin_amdgcn_readlane(incl, 63);
-            if (total == 0) break;
-            const int excl = incl - len;
-            const int take = min(len, max(0, CLIST - excl));
+            T = min(total - skip, CLIST);
+            const int at = incl - len - skip;  // list position of this column's first cluster
+            const int t1 = min(len, T - at);
             wave_sync();  // the previous list has been consumed
-            for (int t = 0; t < take; ++t) {
-                int cl;
-                if (a0 < a1) {
-                    cl = a0++;
-                } else {
-                    cl = b0++;
-                }
-                clist[excl + t] = cl;
+            for (int t = max(0, -at); t < t1; ++t) clist[at + t] = t < la ? a0 + t : b0 + (t - la);
+            skip += T;
+            if (skip >= total) {
+                k0 += 64;
+                skip = 0;
             }
+            if (T == 0) continue;
+            if (lane < 16) clist[T + lane] = 0;  // the last chunk read whole, and one more
             wave_sync();
-            process(min(total, CLIST));
+            tq = 0;
+            load_chunk(0);
+            return true;
+        }
+        return false;
+    };
+    // Tests the chunk of 8 candidate clusters (64 atoms) at clist[tq] and lists the slots
+    // of its survivors.
+    auto search_chunk = [&]() __attribute__((always_inline)) {
+        const uint4 uj = nu;
+        const int slot = nslot;
+        load_chunk(tq + 8);  // past the list: cluster 0, unused
+        const float jx = (float)(int)(uj.x - ucx);
+        const float jy = (float)(int)(uj.y - ucy);
+        const float jz = (float)(int)(uj.z - ucz);
+        const float ex = fmaxf(fmaxf(fmaf(-sx, jx, lox), fmaf(sx, jx, -hix)), 0.0f);
+        const float ey = fmaxf(fmaxf(fmaf(-sy, jy, loy), fmaf(sy, jy, -hiy)), 0.0f);
+        const float ez = fmaxf(fmaxf(fmaf(-sz, jz, loz), fmaf(sz, jz, -hiz)), 0.0f);
+        const unsigned long long m =
+            __builtin_amdgcn_ballot_w64((uj.w != PAD_W) & (fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < rcs2)) &
+            lanes8(T - tq);
+        if (rec) {
+            // masks of 64 candidate clusters (a byte each) gather in LDS; then one record
+            // per cluster with a survivor, in candidate order: cluster index << 8 | mask
+            if (lane == 0) smask[(tq >> 3) & 7] = m;
+            if ((tq & 56) == 56 || tq + 8 >= T) {
+                wave_sync();
+                const int k = (tq & ~63) + lane;
+                const uint32_t mk = reinterpret_cast<const unsigned char*>(smask)[lane];
+                const bool has = (k < T) & (mk != 0u);
+                const unsigned long long nzm = __builtin_amdgcn_ballot_w64(has);
+                const int pos = __builtin_amdgcn_mbcnt_hi(
+                    (unsigned)(nzm >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)nzm, (unsigned)wr));
+                if (has && pos < lcap) nl[pos] = (int)(((uint32_t)clist[k] << 8) | mk);
+                wr += (int)__popcll(nzm);
+                wave_sync();
+            }
+        }
+        append(m, slot);
+        tq += 8;
+    };
+
+    while (refill()) {
+        for (; tq < T;) {
+            search_chunk();
+            if (wp - rp >= 64) batch();
         }
     }
-    // ---- remaining ring entries ---------------------------------------------------
-    if (wp - rp > 0) eval.template operator()<false>(rp, wp - rp);
+    // ---- the batch in flight and the remaining slots ----------------------------------
+    {
+        const int n = wp - rp;
+        if (cur > 0) {
+            to_ring(64);
+            if (n > 0) gather(n);
+            wave_sync();
+            eval.template operator()<true>(64);
+            wave_sync();
+        } else if (n > 0) {
+            gather(n);
+        }
+        if (n > 0) {
+            to_ring(n);
+            wave_sync();
+            eval.template operator()<false>(n);
+        }
+    }
     if (rec && lane == 0) *nlc = wr;
 
     // ---- reduce over the 8 j lanes of each i atom and store ------------------------
@@ -878,7 +922,7 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
 // wave index is made scalar (readfirstlane) and the lane exchanges use swizzles
 // (lane_xor), so that per-wave pointers and shuffle bounds take no vector registers.
 template <int MODE, int N3, int EL, int WE>
-constexpr int PAIR_WAVES = EL == 0 && N3 == 0 && (MODE == 1 || WE == 0) ? 6 : 5;
+constexpr int PAIR_WAVES = EL == 0 && N3 == 0 && (MODE == 1 || WE == 0) ? 6 : (N3 && WE ? 4 : 5);
 
 // One workgroup per PW i-clusters; consecutive workgroups of the logical order
 // (neighbouring clusters) go to one XCD (workgroups are dealt to the 8 XCDs in turn).
@@ -896,13 +940,11 @@ __global__ void __launch_bounds__(64 * PW, (PAIR_WAVES<MODE, N3, EL, WE>))
     const int p = find_seg(L, lblk);
     float4* s_tab = s_dyn;
     float* s_ring = reinterpret_cast<float*>(s_dyn + TAB_COPIES<MODE> * L.ntmax * L.ntmax);
-    int* s_cl = reinterpret_cast<int*>(s_ring + PW * NF * RING);
     load_table<MODE>(segs + p, s_tab, threadIdx.x, 64 * PW);
     __syncthreads();  // the only block barrier: waves are independent from here on
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar indices
     pair_wave<MODE, N3, EL, WE>(segs, L, ws, outsel, energy_bead, lists, bead0, p,
-                                (lblk - L.pf[p]) * PW + wave, s_tab, s_ring + wave * NF * RING,
-                                s_cl + wave * CLIST);
+                                (lblk - L.pf[p]) * PW + wave, s_tab, s_ring + wave * WAVE_LDS<NF>);
 }
 
 // Persistent form: as many workgroups as the GPU holds at once, each taking logical blocks
@@ -926,7 +968,6 @@ __global__ void __launch_bounds__(64 * PW, (PAIR_WAVES<MODE, N3, EL, WE>))
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar indices
     float4* s_tab = s_dyn;
     float* s_ring = reinterpret_cast<float*>(s_dyn + TAB_COPIES<MODE> * L.ntmax * L.ntmax);
-    int* s_cl = reinterpret_cast<int*>(s_ring + PW * NF * RING);
     int cur = -1;
     for (int it = 0;; it ^= 1) {
         if (threadIdx.x == 0) s_next[it] = atomicAdd(queue + x, 1);
@@ -941,8 +982,7 @@ __global__ void __launch_bounds__(64 * PW, (PAIR_WAVES<MODE, N3, EL, WE>))
             cur = p;
         }
         pair_wave<MODE, N3, EL, WE>(segs, L, ws, outsel, energy_bead, lists, bead0, p,
-                                    (lblk - L.pf[p]) * PW + wave, s_tab, s_ring + wave * NF * RING,
-                                    s_cl + wave * CLIST);
+                                    (lblk - L.pf[p]) * PW + wave, s_tab, s_ring + wave * WAVE_LDS<NF>);
     }
 }
 
@@ -987,7 +1027,7 @@ static void launch_pair_t(const SegDev* dsegs, const SegDev* hsegs, const Launch
     const int nblk = L.pf[base.nseg];
     if (nblk == 0) return;
     const size_t tab = TAB_COPIES<MODE> * (size_t)L.ntmax * L.ntmax * sizeof(float4);
-    const size_t wlds = (size_t)Fields<MODE, N3>::NF * RING * sizeof(float) + CLIST * sizeof(int);
+    const size_t wlds = (size_t)WAVE_LDS<Fields<MODE, N3>::NF> * sizeof(float);
     if (persistent) {
         // a grid of what the GPU holds at once: a multiple of 8 workgroups (one set per XCD
         // queue), no more workgroups than logical blocks

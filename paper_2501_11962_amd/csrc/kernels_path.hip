@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(EWB) k_resid(const SegDev* __restrict__ segs, 
             d64[2] = d[2];
             const int slot = wsp<const int>(ws, sg.o_slotof)[(size_t)n * Q + i];
             wsp<float4>(ws, sg.o_vs)[(size_t)n * s.S + slot] =
-                make_float4((float)d[0], (float)d[1], (float)d[2], 0.0f);
+                make_float4((float)d[0], (float)d[1], (float)d[2], __int_as_float(s.key[i]));
             const double d2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
             es = 0.5 * Ki * d2;
             if (!finite3(d[0], d[1], d[2])) flag(cp.status, ST_NONFINITE);
@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(EWB) k_prep_v(const SegDev* __restrict__ segs,
     const double* v = cp.V + sg.roff + ((size_t)b * Q + i) * 3;
     const int slot = wsp<const int>(cp.ws, sg.o_slotof)[(size_t)b * Q + i];
     wsp<float4>(cp.ws, sg.o_vs)[(size_t)b * sg.s.S + slot] =
-        make_float4((float)v[0], (float)v[1], (float)v[2], 0.0f);
+        make_float4((float)v[0], (float)v[1], (float)v[2], __int_as_float(sg.s.key[i]));
 }
 
 // bead_hvp: H v = (H v)_pair + (H v)_bond (FP64 sum, FP32 out).

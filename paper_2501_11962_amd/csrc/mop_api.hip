@@ -362,6 +362,8 @@ static SysDev plan_geometry(const mop_system_s* sys, const mop_plan_opts* opts) 
     }
     s.cw[0] = (float)cwx;
     s.cw[1] = (float)cwy;
+    s.isz = 1.0f / s.sc[2];
+    for (int a = 0; a < 2; ++a) s.iL[a] = 1.0f / s.Lf[a];
     s.rcs = (float)rcs;
     s.rcs2 = (float)(rcs * rcs);
     // neighbour-list capacity in records (one per neighbouring cluster with an atom in

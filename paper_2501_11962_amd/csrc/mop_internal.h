@@ -5,10 +5,11 @@
 //   0.5 nm) and, inside each column, counting-sorted by z bin.  Each column's slot
 //   range is padded to a multiple of 8 so that it splits into 8-atom clusters; padding
 //   slots carry DUMMY_KEY.  Sorted arrays (structure of arrays, one entry per slot):
-//     upos  uint4  {x, y, z fixed point (box = 2^32 units), charge bits (float)}
+//     upos  uint4  {x, y, z fixed point (box = 2^32 units), charge bits (float); PAD_W
+//                  in padding slots}
 //     umeta int2   {16 * exclusion key + LJ type, LJ type}
 //     orig  int    atom index of the slot (-1 for padding)
-//     vs    float4 the vector of a Hessian-vector product, slot order
+//     vs    float4 the vector of a Hessian-vector product and the packed key, slot order
 //     fs    float  x3 pair sums in slot order (structure of arrays), Newton-3 kernels
 //   Per atom (original order): slotof, pair force / pair HVP outputs (float4).
 //   Per cluster: the neighbour list a force pass records for the Hessian pass of the
@@ -41,13 +42,14 @@ namespace mop {
 
 constexpr int MAXSEG = 32;        // paths per launch
 constexpr int CLUSTER = 8;        // atoms per cluster
-constexpr int RING = 128;         // j-atom ring per wave (power of two, >= 2*64)
+constexpr int RING = 64;          // j-atom ring per wave: one evaluation batch
 constexpr int CLIST = 256;        // candidate-cluster list per wave
 constexpr int MAXTYPES = 16;      // LJ types (the type fills the low 4 bits of a packed key)
 constexpr int EWB = 256;          // block size of the elementwise kernels
 constexpr int WAVES_PERSISTENT = 0x100;  // or-ed into a plan's waves: persistent pair launches
 constexpr size_t WS_QUEUE = 64;   // workspace byte offset of the 8 work-queue counters
 constexpr int32_t DUMMY_KEY = INT32_MIN;
+constexpr uint32_t PAD_W = 0xFFFFFFFFu;  // upos.w of a padding slot (a NaN: no charge)
 
 // Status bits (mirrors MOP_DEV_* of the public header).
 constexpr int ST_NONFINITE = 1;
@@ -72,6 +74,8 @@ struct SysDev {
     float sc[3];      // nm per fixed-point unit: L / 2^32
     float Lf[3];
     float cw[2];      // column widths (nm)
+    float isz;        // 1 / sc[2]
+    float iL[2];      // 1 / Lf[0], 1 / Lf[1]
     uint32_t ovr[3];  // OVERLAP_R in fixed-point units per axis, rounded up, plus one
     float rc2;        // cutoff^2
     float rcs;        // neighbour-search radius (cutoff + margin)
