@@ -7,21 +7,23 @@
 // Inside a bin atoms are ordered by index (the histogram's atomic ranks only reserve
 // places), so the slot order, and with it every pair sum, is the same on every call.
 // HBM-bound, O(Q) per bead.
+#include <algorithm>
+
 #include "device_common.h"
 #include "launch.h"
 
 namespace mop {
 
-// Zero the bin histograms, the slot-order pair sums and (zero_dmax) the per-bead
+// Zero the bin histograms, the slot-order pair sums (newton3) and (zero_dmax) the per-bead
 // max |d|^2 of every segment.
 __global__ void __launch_bounds__(EWB) k_zero(const SegDev* __restrict__ segs, Launch L, char* ws,
-                                              int zero_dmax) {
+                                              int zero_dmax, int newton3) {
     const int blk = blockIdx.x;
     const int p = find_seg(L, blk);
     const SegDev& sg = segs[p];
     const size_t idx = (size_t)(blk - L.pf[p]) * EWB + threadIdx.x;
     const size_t n1 = (size_t)L.nb[p] * sg.s.ncol * sg.s.nzb;
-    const size_t n2 = (size_t)L.nb[p] * 3 * sg.s.S;
+    const size_t n2 = newton3 ? (size_t)L.nb[p] * 3 * sg.s.S : 0;
     if (idx < n1) {
         wsp<int>(ws, sg.o_bincnt)[idx] = 0;
     } else if (idx - n1 < n2) {
@@ -222,63 +224,346 @@ __global__ void __launch_bounds__(EWB) k_bin_displace(const SegDev* __restrict__
                    to_fixed(r[2] + eps * d[2], sg.s.L[2]), __float_as_uint(sg.s.qs[i]));
 }
 
-// Overlap check of a binned configuration: the atom of each slot against every atom whose
-// fixed-point coordinates lie within OVERLAP_R of its own along each axis.  Columns and
-// z bins are contiguous ranges of fixed-point values, so those atoms sit in the columns
-// of u_x -/+ d and u_y -/+ d (at most two each, d being far below a column width) and in
-// the z bins from that of u_z - d to that of u_z + d.  A non-excluded pair closer than
-// OVERLAP_R (the same FP32 difference of fixed-point coordinates the pair kernels form)
-// sets ST_OVERLAP in the status word, which leads the workspace.
+// Overlap check of a binned configuration: sets ST_OVERLAP in the status word, which leads
+// the workspace, when a non-excluded pair lies closer than OVERLAP_R (the same FP32
+// difference of fixed-point coordinates the pair kernels form).  Each pair is looked for
+// from one of its atoms:
+//   same column: slots are in the order of the z bins, so the partners of slot si are the
+//     slots after it up to the bin of u_z + d (in most cases the one or two that share
+//     its bin); past the top of the box, the column's first bins too;
+//   neighbouring columns: only for an atom within d of its column's upper x or y face
+//     (d is far below a column width), over the bins from u_z - d to u_z + d.
+// Looking through the bins around every atom instead (two columns per axis, bin bounds
+// read first) took 61 us for 15 beads of 150,000 atoms and 17 of the 28 us of the
+// one-workgroup binning of 3,000.
+// pos(slot) and key(slot) read a slot; first(col, zb) and end(col, zb) give a bin's slots.
+template <class Pos, class Key, class First, class End>
+__device__ __forceinline__ bool overlaps(const SysDev& s, int si, uint32_t ux, uint32_t uy, uint32_t uz,
+                                         int nslots, Pos pos, Key key, First first, End end) {
+    const int ncx = s.ncx, ncy = s.ncy, nzb = s.nzb;
+    const uint32_t d0 = s.ovr[0], d1 = s.ovr[1], d2 = s.ovr[2];
+    bool hit = false;
+    auto test = [&](int sj, const uint4& uj) __attribute__((always_inline)) {
+        const float dx = (float)(int)(uj.x - ux) * s.sc[0];
+        const float dy = (float)(int)(uj.y - uy) * s.sc[1];
+        const float dz = (float)(int)(uj.z - uz) * s.sc[2];
+        const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+        if (r2 < OVERLAP_R2) hit |= abs((key(si) >> 4) - (key(sj) >> 4)) > 2;
+    };
+    const int cx = fixed_bin(ux, ncx), cy = fixed_bin(uy, ncy);
+    // upper end of the z bins to look through; all of them after a wrap (d < box height)
+    const uint32_t zt = uz + d2;
+    const int zb1 = zt < uz ? nzb - 1 : fixed_bin(zt, nzb);
+    for (int sj = si + 1; sj < nslots; ++sj) {
+        const uint4 uj = pos(sj);
+        if (uj.w == PAD_W || fixed_bin(uj.z, nzb) > zb1 || fixed_bin(uj.x, ncx) != cx ||
+            fixed_bin(uj.y, ncy) != cy)
+            break;
+        test(sj, uj);
+    }
+    auto bins = [&](int col, int za, int zb) __attribute__((always_inline)) {  // za .. zb, wrapping
+        for (int z = za;; z = z + 1 == nzb ? 0 : z + 1) {
+            const int e = end(col, z);
+            for (int sj = first(col, z); sj < e; ++sj)
+                if (sj != si) test(sj, pos(sj));
+            if (z == zb) break;
+        }
+    };
+    if (zt < uz) bins(cx * ncy + cy, 0, fixed_bin(zt, nzb));
+    const int x1 = fixed_bin(ux + d0, ncx), y1 = fixed_bin(uy + d1, ncy);
+    if (x1 != cx || y1 != cy) {
+        const int y0 = fixed_bin(uy - d1, ncy), z0 = fixed_bin(uz - d2, nzb), z1 = fixed_bin(zt, nzb);
+        if (y1 != cy) bins(cx * ncy + y1, z0, z1);
+        if (x1 != cx) {
+            bins(x1 * ncy + cy, z0, z1);
+            if (y1 != cy) bins(x1 * ncy + y1, z0, z1);
+            if (y0 != cy && y0 != y1) bins(x1 * ncy + y0, z0, z1);
+        }
+    }
+    return hit;
+}
+
 __global__ void __launch_bounds__(EWB) k_overlap(const SegDev* __restrict__ segs, Launch L, char* ws) {
     const int blk = blockIdx.x;
     const int p = find_seg(L, blk);
     const SegDev& sg = segs[p];
     const int local = blk - L.pf[p];
-    const int S = sg.s.S, ncx = sg.s.ncx, ncy = sg.s.ncy, nzb = sg.s.nzb;
+    const int S = sg.s.S, nzb = sg.s.nzb;
     const int bps = (S + EWB - 1) / EWB;  // blocks per bead (slot order)
     const int b = local / bps;
     const int si = (local - b * bps) * EWB + threadIdx.x;
-    if (si >= S) return;
+    const int* cs = wsp<const int>(ws, sg.o_colstart) + (size_t)b * (sg.s.ncol + 1);
+    const int ns = cs[sg.s.ncol];
+    if (si >= ns) return;  // slots past the last column hold no atom
     const uint4* up = wsp<const uint4>(ws, sg.o_upos) + (size_t)b * S;
     const int2* um = wsp<const int2>(ws, sg.o_umeta) + (size_t)b * S;
-    const int* cs = wsp<const int>(ws, sg.o_colstart) + (size_t)b * (sg.s.ncol + 1);
     const int* bo = wsp<const int>(ws, sg.o_binoff) + (size_t)b * sg.s.ncol * (nzb + 1);
-    const int2 mi = um[si];
-    // slots past the last column and padding slots hold no atom
-    if (si >= cs[sg.s.ncol] || mi.x == DUMMY_KEY) return;
     const uint4 ui = up[si];
-    const int ki = mi.x >> 4;
-    const uint32_t* dr = sg.s.ovr;  // OVERLAP_R in fixed-point units per axis, with margin
-    const int x0 = fixed_bin(ui.x - dr[0], ncx), x1 = fixed_bin(ui.x + dr[0], ncx);
-    const int y0 = fixed_bin(ui.y - dr[1], ncy), y1 = fixed_bin(ui.y + dr[1], ncy);
-    const int z0 = fixed_bin(ui.z - dr[2], nzb), z1 = fixed_bin(ui.z + dr[2], nzb);
-    const float sx = sg.s.sc[0], sy = sg.s.sc[1], sz = sg.s.sc[2];
+    if (ui.w == PAD_W) return;
+    const bool hit = overlaps(
+        sg.s, si, ui.x, ui.y, ui.z, ns, [&](int sj) { return up[sj]; }, [&](int sj) { return um[sj].x; },
+        [&](int col, int z) { return cs[col] + bo[(size_t)col * (nzb + 1) + z]; },
+        [&](int col, int z) { return cs[col] + bo[(size_t)col * (nzb + 1) + z + 1]; });
+    if (hit) atomicOr(reinterpret_cast<int*>(ws), ST_OVERLAP);
+}
+
+// ---- one bead per workgroup ---------------------------------------------------------
+// The whole binning of a bead in one workgroup whose bin counts and reserved places fit the
+// LDS: the eight kernels above cost a launch and a trip through memory each, which is what
+// bounds them on small systems (3-5 us each; 27 of the 58 us of a gradient of 256 atoms x
+// 32 beads), and global atomics bound the counting on larger ones.  Same slots, same arrays.
+//   J > 0    atoms per thread at most (Q <= 1024 J), kept in registers, positions in LDS.
+//            The overlap check is done here too: pairs of one bin while the bin is ordered,
+//            then the few atoms within OVERLAP_R of an upper bin face against the bins
+//            beyond it, as a list of (atom, bin) tasks spread over all threads.
+//   J == 0   more atoms: coordinates and ranks wait in the workspace; k_overlap follows
+constexpr int FB = 1024;           // threads
+constexpr int FUSED_COLS = 1024;   // columns at most (one per thread in the column scan)
+constexpr size_t FUSED_LDS = 144 * 1024;
+
+constexpr int TASKS = 2048;        // overlap tasks held (more are done where they arise)
+
+static size_t fused_lds(const SysDev& s, bool regs) {
+    const size_t bins = (size_t)s.ncol * s.nzb;
+    return bins * 4 + (((size_t)s.S * 2 + 3) & ~(size_t)3) + (regs ? (size_t)s.Q * 12 + TASKS * 4 : 0);
+}
+constexpr int FUSED_J = 4;
+static bool fused_regs(const SysDev& s) {
+    return s.Q <= FB * FUSED_J && s.ncol <= FUSED_COLS && (size_t)s.ncol * s.nzb <= 65536 &&
+           fused_lds(s, true) <= FUSED_LDS;
+}
+static bool fused_any(const SysDev& s) {
+    return s.Q <= 65535 && s.ncol <= FUSED_COLS && fused_lds(s, false) <= FUSED_LDS;
+}
+
+template <int J>
+__global__ void __launch_bounds__(FB) k_bin_bead(const SegDev* __restrict__ segs, Launch L, char* ws,
+                                                 const double* __restrict__ R, int fdsign, double fdh,
+                                                 int newton3) {
+    extern __shared__ int s_bin[];  // counts, then offsets inside the column
+    __shared__ int s_cnt[FUSED_COLS], s_start[FUSED_COLS + 1], s_wave[FB / 64], s_ntask;
+    constexpr bool REGS = J > 0;
+    constexpr int NJ = REGS ? J : 1;
+    const int p = find_seg(L, blockIdx.x);
+    const SegDev& sg = segs[p];
+    const int b = (int)blockIdx.x - L.pf[p];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int Q = sg.s.Q, S = sg.s.S, ncol = sg.s.ncol, nzb = sg.s.nzb, ncx = sg.s.ncx, ncy = sg.s.ncy;
+    const int nbin = ncol * nzb;
+    unsigned short* s_tmp = reinterpret_cast<unsigned short*>(s_bin + nbin);
+    uint32_t* s_x = reinterpret_cast<uint32_t*>(s_tmp + ((S + 1) & ~1));
+    uint32_t *s_y = s_x + Q, *s_z = s_y + Q, *s_task = s_z + Q;  // (J > 0) by atom
+    uint4* upos = wsp<uint4>(ws, sg.o_upos) + (size_t)b * S;
+    int2* umeta = wsp<int2>(ws, sg.o_umeta) + (size_t)b * S;
+    int* orig = wsp<int>(ws, sg.o_orig) + (size_t)b * S;
+    int* slotof = wsp<int>(ws, sg.o_slotof) + (size_t)b * Q;
+    uint4* atomu = wsp<uint4>(ws, sg.o_atomu) + (size_t)b * Q;
+    int* rankg = wsp<int>(ws, sg.o_rank) + (size_t)b * Q;
+    int* binoff = wsp<int>(ws, sg.o_binoff) + (size_t)b * ncol * (nzb + 1);
+    int* colstart = wsp<int>(ws, sg.o_colstart) + (size_t)b * (ncol + 1);
+
+    double eps = 0.0;
+    const double* dis = nullptr;
+    if (fdsign != 0) {
+        const double m2 = __longlong_as_double((long long)wsp<unsigned long long>(ws, sg.o_dmax)[b]);
+        eps = m2 > 0.0 ? fdsign * fdh / sqrt(m2) : 0.0;
+        dis = wsp<const double>(ws, sg.o_d64) + (size_t)b * Q * 3;
+    } else if (tid == 0) {
+        wsp<unsigned long long>(ws, sg.o_dmax)[b] = 0ull;
+    }
+    for (int t = tid; t < nbin; t += FB) s_bin[t] = 0;
+    if (tid == 0) s_ntask = 0;
+    if (newton3) {  // the slot-order pair sums of the Newton-3 kernels
+        float* fs = wsp<float>(ws, sg.o_fs) + (size_t)b * 3 * S;
+        for (int t = tid; t < 3 * S; t += FB) fs[t] = 0.0f;
+    }
+    __syncthreads();
+
+    // counts and ranks.  .w: column << 20 | z bin (z bins are below 2^16 here)
+    uint4 u[NJ];
+    int rk[NJ];
+    const double* Rb = R + sg.roff + (size_t)b * Q * 3;
+    auto count = [&](int i, uint4& v, int& rank) __attribute__((always_inline)) {
+        double x = Rb[3 * (size_t)i], y = Rb[3 * (size_t)i + 1], z = Rb[3 * (size_t)i + 2];
+        if (fdsign != 0) {
+            x += eps * dis[3 * (size_t)i];
+            y += eps * dis[3 * (size_t)i + 1];
+            z += eps * dis[3 * (size_t)i + 2];
+        }
+        v.x = to_fixed(x, sg.s.L[0]);
+        v.y = to_fixed(y, sg.s.L[1]);
+        v.z = to_fixed(z, sg.s.L[2]);
+        const int col = fixed_bin(v.x, ncx) * ncy + fixed_bin(v.y, ncy), zb = fixed_bin(v.z, nzb);
+        v.w = ((uint32_t)col << 20) | (uint32_t)zb;
+        rank = atomicAdd(s_bin + col * nzb + zb, 1);
+    };
+    if constexpr (REGS) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (tid + j * FB < Q) {
+                const int i = tid + j * FB;
+                count(i, u[j], rk[j]);
+                s_x[i] = u[j].x;
+                s_y[i] = u[j].y;
+                s_z[i] = u[j].z;
+            }
+    } else {
+        for (int i = tid; i < Q; i += FB) {
+            count(i, u[0], rk[0]);
+            atomu[i] = u[0];
+            rankg[i] = rk[0];
+        }
+    }
+    __syncthreads();
+
+    // z-bin offsets inside each column, one wave per column
+    const int per = (nzb + 63) >> 6;
+    for (int col = wave; col < ncol; col += FB / 64) {
+        int* cnt = s_bin + col * nzb;
+        int* off = binoff + (size_t)col * (nzb + 1);
+        const int z0 = min(lane * per, nzb), z1 = min(z0 + per, nzb);
+        int sum = 0;
+        for (int z = z0; z < z1; ++z) sum += cnt[z];
+        const int incl = wave_incl_scan(sum);
+        int run = incl - sum;
+        for (int z = z0; z < z1; ++z) {
+            const int c = cnt[z];
+            cnt[z] = run;
+            off[z] = run;
+            run += c;
+        }
+        if (lane == 63) {
+            off[nzb] = incl;
+            s_cnt[col] = incl;
+            wsp<int>(ws, sg.o_colcnt)[(size_t)b * ncol + col] = incl;
+        }
+    }
+    __syncthreads();
+    // first slot of each column (counts padded to whole clusters)
+    {
+        const int v = tid < ncol ? (s_cnt[tid] + 7) & ~7 : 0;
+        const int incl = wave_incl_scan(v);
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        int base = 0;
+        for (int k = 0; k < wave; ++k) base += s_wave[k];
+        if (tid < ncol) {
+            s_start[tid] = base + incl - v;
+            colstart[tid] = base + incl - v;
+        }
+        if (tid == FB - 1) {
+            s_start[ncol] = base + incl;
+            colstart[ncol] = base + incl;
+        }
+    }
+    __syncthreads();
+    // reserve places in rank order, then place each atom after the atoms of its bin with a
+    // smaller index
+    auto first_of = [&](uint32_t w) __attribute__((always_inline)) {
+        const int col = (int)(w >> 20), zb = (int)(w & 0xFFFFFu);
+        return s_start[col] + s_bin[col * nzb + zb];
+    };
+    if constexpr (REGS) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (tid + j * FB < Q) s_tmp[first_of(u[j].w) + rk[j]] = (unsigned short)(tid + j * FB);
+    } else {
+        for (int i = tid; i < Q; i += FB) s_tmp[first_of(atomu[i].w) + rankg[i]] = (unsigned short)i;
+    }
+    __syncthreads();
     bool hit = false;
-    for (int a = 0; a < 2; ++a) {
-        const int cx = a ? x1 : x0;
-        if (a && x1 == x0) break;
-        for (int c = 0; c < 2; ++c) {
-            const int cy = c ? y1 : y0;
-            if (c && y1 == y0) break;
-            const int col = cx * ncy + cy;
-            const int base = cs[col];
-            const int* o = bo + (size_t)col * (nzb + 1);
-            for (int zb = z0;; zb = zb + 1 == nzb ? 0 : zb + 1) {
-                for (int sj = base + o[zb]; sj < base + o[zb + 1]; ++sj) {
-                    if (sj == si) continue;
-                    const uint4 uj = up[sj];
-                    const int kj = um[sj].x >> 4;
-                    const float dx = (float)(int)(uj.x - ui.x) * sx;
-                    const float dy = (float)(int)(uj.y - ui.y) * sy;
-                    const float dz = (float)(int)(uj.z - ui.z) * sz;
-                    const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                    hit |= (r2 < OVERLAP_R2) & (abs(ki - kj) > 2);
-                }
-                if (zb == z1) break;
+    // atoms i and k closer than OVERLAP_R (see k_overlap) and not excluded (J > 0)
+    auto near = [&](int i, const uint4& v, int k) __attribute__((always_inline)) {
+        const float dx = (float)(int)(s_x[k] - v.x) * sg.s.sc[0];
+        const float dy = (float)(int)(s_y[k] - v.y) * sg.s.sc[1];
+        const float dz = (float)(int)(s_z[k] - v.z) * sg.s.sc[2];
+        if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < OVERLAP_R2)
+            hit |= abs((sg.s.key[i] >> 4) - (sg.s.key[k] >> 4)) > 2;
+    };
+    auto bin_end = [&](int bin) __attribute__((always_inline)) {
+        const int col = bin / nzb;
+        return bin - col * nzb + 1 < nzb ? s_bin[bin + 1] : s_cnt[col];
+    };
+    auto place = [&](int i, const uint4& v) __attribute__((always_inline)) {
+        const int col = (int)(v.w >> 20), zb = (int)(v.w & 0xFFFFFu);
+        const int off = s_bin[col * nzb + zb];
+        const int n = (zb + 1 < nzb ? s_bin[col * nzb + zb + 1] : s_cnt[col]) - off;
+        const int first = s_start[col] + off;
+        int r = 0;
+        for (int k = 0; k < n; ++k) {
+            const int o = s_tmp[first + k];
+            r += o < i;
+            if (REGS && o > i) near(i, v, o);
+        }
+        const int slot = first + r;
+        upos[slot] = make_uint4(v.x, v.y, v.z, __float_as_uint(sg.s.qs[i]));
+        umeta[slot] = make_int2(sg.s.key[i], sg.s.type[i]);
+        orig[slot] = i;
+        slotof[i] = slot;
+    };
+    // (J > 0) atom i against every atom of a bin
+    auto scan_bin = [&](int i, const uint4& v, int bin) __attribute__((always_inline)) {
+        const int base = s_start[bin / nzb], e = base + bin_end(bin);
+        for (int k = base + s_bin[bin]; k < e; ++k)
+            if ((int)s_tmp[k] != i) near(i, v, s_tmp[k]);
+    };
+    // (J > 0) the bins beyond the upper faces that atom i is near (every pair of bins is
+    // looked at from the lower one; x-y neighbours over the bins of u_z -/+ d)
+    auto faces = [&](int i, const uint4& v) __attribute__((always_inline)) {
+        const int cx = fixed_bin(v.x, ncx), cy = fixed_bin(v.y, ncy), zb = (int)(v.w & 0xFFFFFu);
+        auto add = [&](int col, int za, int ze) {
+            for (int z = za;; z = z + 1 == nzb ? 0 : z + 1) {
+                const int bin = col * nzb + z;
+                const int t = atomicAdd(&s_ntask, 1);
+                if (t < TASKS) s_task[t] = (uint32_t)i << 16 | (uint32_t)bin;
+                else scan_bin(i, v, bin);
+                if (z == ze) break;
+            }
+        };
+        const uint32_t* d = sg.s.ovr;
+        const int z1 = fixed_bin(v.z + d[2], nzb);
+        if (z1 != zb) add(cx * ncy + cy, zb + 1 == nzb ? 0 : zb + 1, z1);
+        const int x1 = fixed_bin(v.x + d[0], ncx), y1 = fixed_bin(v.y + d[1], ncy);
+        if (x1 != cx || y1 != cy) {
+            const int y0 = fixed_bin(v.y - d[1], ncy), z0 = fixed_bin(v.z - d[2], nzb);
+            if (y1 != cy) add(cx * ncy + y1, z0, z1);
+            if (x1 != cx) {
+                add(x1 * ncy + cy, z0, z1);
+                if (y1 != cy) add(x1 * ncy + y1, z0, z1);
+                if (y0 != cy && y0 != y1) add(x1 * ncy + y0, z0, z1);
+            }
+        }
+    };
+    if constexpr (REGS) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (tid + j * FB < Q) {
+                place(tid + j * FB, u[j]);
+                faces(tid + j * FB, u[j]);
+            }
+    } else {
+        for (int i = tid; i < Q; i += FB) place(i, atomu[i]);
+    }
+    __syncthreads();
+    if (REGS) {
+        for (int t = tid; t < min(s_ntask, TASKS); t += FB) {
+            const int i = (int)(s_task[t] >> 16);
+            scan_bin(i, make_uint4(s_x[i], s_y[i], s_z[i], 0u), (int)(s_task[t] & 0xFFFFu));
+        }
+        if (hit) atomicOr(reinterpret_cast<int*>(ws), ST_OVERLAP);
+    }
+    // padding slots of each column
+    if (tid < ncol) {
+        const int n = s_cnt[tid], base = s_start[tid], pad = (n + 7) & ~7;
+        if (pad > n) {
+            const uint4 last = upos[base + n - 1];
+            for (int k = base + n; k < base + pad; ++k) {
+                upos[k] = make_uint4(last.x, last.y, last.z, PAD_W);
+                umeta[k] = make_int2(DUMMY_KEY, 0);
+                orig[k] = -1;
             }
         }
     }
-    if (hit) atomicOr(reinterpret_cast<int*>(ws), ST_OVERLAP);
 }
 
 void run_displace(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char* ws,
@@ -295,19 +580,76 @@ void run_displace(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, 
     hipLaunchKernelGGL(k_bin_pad, dim3(Lc.pf[base.nseg]), dim3(EWB), 0, st, dsegs, Lc, ws);
 }
 
+template <int J>
+static void launch_bead(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, const char* which,
+                        char* ws, const double* R, int fdsign, double fdh, int newton3, hipStream_t st) {
+    Launch L = base;
+    L.pf[0] = 0;
+    size_t lds = 0;
+    for (int p = 0; p < base.nseg; ++p) {
+        const bool mine = which[p] == (J > 0 ? 1 : 2);
+        L.pf[p + 1] = L.pf[p] + (mine ? base.nb[p] : 0);
+        if (mine) lds = std::max(lds, fused_lds(hsegs[p].s, J > 0));
+    }
+    if (L.pf[base.nseg] == 0) return;
+    hipLaunchKernelGGL(k_bin_bead<J>, dim3(L.pf[base.nseg]), dim3(FB), lds, st, dsegs, L, ws, R, fdsign, fdh,
+                       newton3);
+}
+
+static void bin_general(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char* ws,
+                        const double* R, int fdsign, double fdh, int newton3, hipStream_t st);
+
+static void launch_overlap(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char* ws,
+                           hipStream_t st) {
+    Launch L = base;  // one thread per slot
+    L.pf[0] = 0;
+    for (int p = 0; p < base.nseg; ++p)
+        L.pf[p + 1] = L.pf[p] + base.nb[p] * ((hsegs[p].s.S + EWB - 1) / EWB);
+    if (L.pf[base.nseg] > 0)
+        hipLaunchKernelGGL(k_overlap, dim3(L.pf[base.nseg]), dim3(EWB), 0, st, dsegs, L, ws);
+}
+
 void run_binning(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char* ws,
-                 const double* R, int fdsign, double fdh, hipStream_t st) {
+                 const double* R, int fdsign, double fdh, int newton3, hipStream_t st) {
+    // One workgroup per bead (k_bin_bead) or eight kernels over all beads.  With its atoms
+    // in registers the first is faster for any number of beads: 24 against 47 us for 64
+    // beads of 3,000 atoms, 10 against 25 for one of 256.  Beyond, a workgroup takes about
+    // 12 us + 3.4 ns per atom whatever the number of beads, the eight kernels 28 us +
+    // 0.086 ns per atom and bead (measured from 5,000 x 1 to 30,000 x 32; 140 against 221
+    // us for 96 beads of 22,999), which cross at atoms x (40 - beads) = 186,000.
+    char which[MAXSEG] = {};
+    Launch G = base, O = base;  // beads binned by the eight kernels / with the overlap check apart
+    bool rest = false, one = false, two = false;
+    long long beads = 0;
+    for (int p = 0; p < base.nseg; ++p) beads += base.nb[p];
+    for (int p = 0; p < base.nseg; ++p) {
+        const SysDev& s = hsegs[p].s;
+        which[p] = fused_regs(s) ? 1 : fused_any(s) && s.Q * (40 - beads) <= 186000 ? 2 : 0;
+        if (which[p]) G.nb[p] = 0;
+        if (which[p] == 1) O.nb[p] = 0;
+        one = one || which[p] == 1;
+        two = two || which[p] == 2;
+        rest = rest || (!which[p] && base.nb[p] > 0);
+    }
+    if (one) launch_bead<FUSED_J>(dsegs, hsegs, base, which, ws, R, fdsign, fdh, newton3, st);
+    if (two) launch_bead<0>(dsegs, hsegs, base, which, ws, R, fdsign, fdh, newton3, st);
+    if (rest) bin_general(dsegs, hsegs, G, ws, R, fdsign, fdh, newton3, st);
+    launch_overlap(dsegs, hsegs, O, ws, st);
+}
+
+static void bin_general(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char* ws,
+                        const double* R, int fdsign, double fdh, int newton3, hipStream_t st) {
     Launch L = base;
     // zero histograms (+ max |d|^2 when not binning a displaced configuration)
     L.pf[0] = 0;
     for (int p = 0; p < base.nseg; ++p) {
         const size_t n = (size_t)base.nb[p] * hsegs[p].s.ncol * hsegs[p].s.nzb +
-                         (size_t)base.nb[p] * 3 * hsegs[p].s.S +
+                         (newton3 ? (size_t)base.nb[p] * 3 * hsegs[p].s.S : 0) +
                          (fdsign == 0 ? hsegs[p].maxN : 0);
         L.pf[p + 1] = L.pf[p] + (int)((n + EWB - 1) / EWB);
     }
     if (L.pf[base.nseg] > 0) hipLaunchKernelGGL(k_zero, dim3(L.pf[base.nseg]), dim3(EWB), 0, st, dsegs, L, ws,
-                                                 fdsign == 0 ? 1 : 0);
+                                                 fdsign == 0 ? 1 : 0, newton3);
     // atoms
     Launch La = base;
     La.pf[0] = 0;
@@ -330,11 +672,6 @@ void run_binning(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, c
     hipLaunchKernelGGL(k_bin_scatter, dim3(La.pf[base.nseg]), dim3(EWB), 0, st, dsegs, La, ws);
     hipLaunchKernelGGL(k_bin_place, dim3(La.pf[base.nseg]), dim3(EWB), 0, st, dsegs, La, ws);
     hipLaunchKernelGGL(k_bin_pad, dim3(Lc.pf[base.nseg]), dim3(EWB), 0, st, dsegs, Lc, ws);
-    Launch Ls = base;  // overlap check: one thread per slot
-    Ls.pf[0] = 0;
-    for (int p = 0; p < base.nseg; ++p)
-        Ls.pf[p + 1] = Ls.pf[p] + base.nb[p] * ((hsegs[p].s.S + EWB - 1) / EWB);
-    hipLaunchKernelGGL(k_overlap, dim3(Ls.pf[base.nseg]), dim3(EWB), 0, st, dsegs, Ls, ws);
 }
 
 }  // namespace mop

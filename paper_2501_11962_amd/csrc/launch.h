@@ -5,9 +5,10 @@
 
 namespace mop {
 
-// Bin every pair bead (fdsign: 0 = R, +1 / -1 = R -/+ eps d for the FD term).
+// Bin every pair bead (fdsign: 0 = R, +1 / -1 = R -/+ eps d for the FD term); newton3: also
+// clear the slot-order sums of the Newton-3 pair kernels.
 void run_binning(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char* ws,
-                 const double* R, int fdsign, double fdh, hipStream_t st);
+                 const double* R, int fdsign, double fdh, int newton3, hipStream_t st);
 
 // Shared-bin finite differences: rewrite the coordinates of the current slots with
 // R + fdsign * eps d (binning of R kept).

@@ -905,7 +905,7 @@ int bead_forces(mop_plan plan, const double* R, int32_t B, float* F, double* U, 
         fork_side(plan, st);
         pme_forces(plan, B, cp, 0, 3, true, mesh_stream(plan, st));
     }
-    run_binning(plan->dseg, &plan->hseg, L, cp.ws, R, 0, 0.0, st);
+    run_binning(plan->dseg, &plan->hseg, L, cp.ws, R, 0, 0.0, plan->newton3, st);
     run_pair(plan->dseg, &plan->hseg, L, cp.ws, 0, 0, U ? -2 : -1, plan->waves, plan->newton3, st);
     if (pme) join_side(plan, st);
     run_finalize_forces(plan->dseg, &plan->hseg, L, cp, st);
@@ -932,7 +932,7 @@ int bead_forces_static(mop_plan plan, const double* R, int32_t B, float* F, doub
     // the array keeps the previous call's contents: start from a clear status word (a
     // kernel, not a memset, so that the call can be captured in a graph)
     run_status_clear(cp.status, st);
-    run_binning(plan->dseg, &plan->hseg, L, cp.ws, R, 0, 0.0, st);
+    run_binning(plan->dseg, &plan->hseg, L, cp.ws, R, 0, 0.0, plan->newton3, st);
     run_pair(plan->dseg, &plan->hseg, L, cp.ws, 0, 0, U ? -2 : -1, plan->waves, 0, st);
     run_finalize_forces(plan->dseg, &plan->hseg, L, cp, st);
     if (status) run_status_copy(cp.status, status, st);
@@ -950,7 +950,7 @@ int bead_hvp(mop_plan plan, const double* R, const double* V, int32_t B, float* 
     cp.Fout = HV;
     const Launch L = one_path(B, B);
     const bool pme = plan->hseg.s.elec == 1;
-    run_binning(plan->dseg, &plan->hseg, L, cp.ws, R, 0, 0.0, st);
+    run_binning(plan->dseg, &plan->hseg, L, cp.ws, R, 0, 0.0, plan->newton3, st);
     if (pme) {
         // after the binning, which clears the per-bead max |v|^2
         fork_side(plan, st);
@@ -984,7 +984,7 @@ static void path_sequence(const SegDev* dsegs, const SegDev* hsegs, const Launch
         pme_forces(pl, base.nb[0], cp, 0, 3, true, pl->side);
     }
     // forces of beads 1..N-1 (bead 1 alone for N = 1), energy of bead 1
-    run_binning(dsegs, hsegs, base, cp.ws, cp.R, 0, 0.0, st);
+    run_binning(dsegs, hsegs, base, cp.ws, cp.R, 0, 0.0, n3, st);
     mark(1);
     // exact gradients: the force pass records neighbour lists for the Hessian pass; with
     // shared-bin finite differences, for the two displaced force passes
@@ -1019,7 +1019,7 @@ static void path_sequence(const SegDev* dsegs, const SegDev* hsegs, const Launch
         if (any && mode != 0) {
             // mode 1 re-bins each displaced configuration; mode 2 keeps R's binning
             for (int sgn : {+1, -1}) {
-                if (mode == 1) run_binning(dsegs, hsegs, Lh, cp.ws, cp.R, sgn, cp.fd_h, st);
+                if (mode == 1) run_binning(dsegs, hsegs, Lh, cp.ws, cp.R, sgn, cp.fd_h, n3, st);
                 else run_displace(dsegs, hsegs, Lh, cp.ws, cp.R, sgn, cp.fd_h, st);
                 run_pair(dsegs, hsegs, Lh, cp.ws, 0, sgn > 0 ? 1 : 2, -1, waves, n3, st,
                          mode == 2 ? 2 * lists : 0);
