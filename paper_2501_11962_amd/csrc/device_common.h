@@ -69,14 +69,24 @@ __device__ __forceinline__ double lane_xor(double v) {
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-__device__ __forceinline__ int wave_incl_scan(int v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(v, d, 64);
-        if (lane >= d) v += t;
-    }
+// Inclusive scans over the 64 lanes of a wave: shifts by 1, 2, 4, 8 inside rows of 16 lanes,
+// then the last lane of each row to the rows after it (data-parallel moves, no LDS).
+// Lanes without a source take `none`, the operation's neutral element.
+template <class Op>
+__device__ __forceinline__ int wave_scan(int v, int none, Op op) {
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x112, 0xF, 0xF, false));  // row_shr:2
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x114, 0xF, 0xF, false));  // row_shr:4
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x118, 0xF, 0xF, false));  // row_shr:8
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    v = op(v, __builtin_amdgcn_update_dpp(none, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
     return v;
+}
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    return wave_scan(v, 0, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int wave_incl_max(int v) {  // v >= 0
+    return wave_scan(v, 0, [](int a, int b) { return max(a, b); });
 }
 
 // Sum over the 64 lanes of a wave (pairwise: lanes 32 apart first, then 16, ..., 1).

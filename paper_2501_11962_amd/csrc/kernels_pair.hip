@@ -78,11 +78,13 @@ namespace mop {
 constexpr int EB = RING;
 static_assert(EB == 64, "evaluation batch");
 
-// Ring of j-atoms, one per wave in LDS (ints stored as float bits; the key word is the
-// packed 16 * exclusion key + LJ type of the system's key table).  Full-shell kernels keep
-// entries as float4 {x, y, z, q} followed by float4 {key, v_x, v_y, v_z} (Hessian) or a
-// float {key} (force), so a step reads a j-atom with one or two 16-byte loads.  The
-// Newton-3 kernels keep one array per field [field][entry], F_* below.
+// Ring of j-atoms, one per wave in LDS.  Full-shell kernels keep entries as float4 {x, y,
+// z, q} followed by float4 {w, v_x, v_y, v_z} (Hessian) or a float {w} (force), so a step
+// reads a j-atom with one or two 16-byte loads.  Integers are stored as float bits: w is
+// the packed 16 * exclusion key + LJ type of the system's key table, or (Ewald kernels, see
+// XSKIP) the byte offset of the type in a table row, with the packed key as one more float
+// that only batches with excluded pairs read.  The Newton-3 kernels keep one array per
+// field [field][entry], F_* below.
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int F_X = 0, F_Y = 1, F_Z = 2, F_Q = 3, F_K = 4, F_S = 5, F_J = 6;
@@ -111,13 +113,33 @@ __device__ __forceinline__ float erfcx_poly(float x) {
 // 32-bit words of LDS per wave: ring, candidate clusters (16 more, so that chunks can be
 // read whole and ahead), slots of survivors, survivor masks of 64 candidate clusters.
 constexpr int SLOTS = 128;  // power of two, at least 63 + 64
-template <int NF>
-constexpr int WAVE_LDS = NF * RING + (CLIST + 16) + SLOTS + 16;
+// Bit map (hash of the cluster index) of the clusters that hold an excluded partner of the
+// i-cluster, itself among them: at most 33 of 4,096 bits set.  Candidates from other
+// clusters cannot be excluded (XSKIP kernels).
+constexpr int XMAP = 128;   // words (XSKIP kernels)
+// The flag of such a cluster: bit 23 of its index in the candidate list, which makes it bit
+// 26 of a listed slot and bit 31 of a neighbour-list record.  Layouts of 2^26 slots or more
+// have no room for it (and no lists), and repeated keys no map to the atoms; there every
+// batch is tested.
+constexpr int XFLAG = 1 << 23;
+constexpr int XSLOT = XFLAG * CLUSTER;
+template <class F>
+constexpr int WAVE_LDS = F::NF * RING + (CLIST + 16) + SLOTS + 16 + F::X;
 
-template <int MODE, int N3>
+// Kernels that skip the exclusion test in batches without excluded pairs.  About 3 of 4
+// batches are such.  The Ewald kernels then save the test, the selects between pair term
+// and correction and the self test: 10.8 -> 10.3 ms per call on the 150,000-atom workload.
+// The reaction-field kernels would save a subtraction and a compare per step and were 2-4%
+// slower with it: their VALU time then falls below what LDS and instruction fetch take.
+template <int N3, int EL>
+constexpr bool XSKIP = N3 == 0 && EL == 1;
+
+template <int MODE, int N3, int EL>
 struct Fields {
-    static constexpr int V = N3 ? F_J + 3 : F_K + 1;  // v_j (HVP only)
-    static constexpr int NF = MODE == 1 ? V + 3 : V;
+    static constexpr int V = F_J + 3;  // v_j (Newton-3 HVP)
+    static constexpr int K = MODE == 1 ? 8 : 5;  // packed key of XSKIP kernels
+    static constexpr int NF = N3 ? (MODE == 1 ? V + 3 : V) : K + (XSKIP<N3, EL> ? 1 : 0);
+    static constexpr int X = XSKIP<N3, EL> ? XMAP : 0;
 };
 
 struct IAtom {
@@ -148,12 +170,14 @@ constexpr bool THREE_Q = MODE == 1 && N3 == 0 && EL == 0;
 // power, which the kernels are short of (they run at 1.8-2.1 GHz of the GPU's 2.4).
 // Every fused multiply-add is written out (contraction is off), so that the variants of
 // the kernels agree bit for bit.
+// toff: byte offset of type j in the table row (XSKIP kernels; the others take the type
+// from kj); EXCL: the pair may be excluded (kj is read).
 // round3: r^-3 is rounded before it is taken from 2 k_rf (force, reaction field).
-template <int MODE, bool EX, bool WANTE, bool T_OUT, int EL, bool Q3 = false>
+template <int MODE, bool EX, bool WANTE, bool T_OUT, int EL, bool Q3, bool EXCL>
 __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const float4* tabrow,
                                           int ntab,
                                           float jx, float jy, float jz,
-                                          float qj, uint32_t kj, float vjx, float vjy,
+                                          float qj, uint32_t toff, uint32_t kj, float vjx, float vjy,
                                           float vjz, bool valid, float& ax, float& ay,
                                           float& az, float& tx, float& ty, float& tz,
                                           float& en, bool round3 = false) {
@@ -173,17 +197,19 @@ __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const 
     // below 2^27, no wrap-around): it lies in [0, 79] exactly when |key_i - key_j| <= 2
     // (same molecule within two chain positions), and in [32, 47] for the atom itself
     const uint32_t kd = I.kp - kj;
-    const int tj = (int)(kj & 15u);
-    const bool exc = kd <= 79u;
+    const bool exc = EXCL && kd <= 79u;
     // Ewald: excluded partners carry a correction, the atom itself nothing
-    const bool act = EL == 1 ? kd - 32u > 15u : !exc;
+    const bool act = !EXCL || (EL == 1 ? kd - 32u > 15u : !exc);
     if (T_OUT) tx = ty = tz = 0.0f;
     if (valid & I.v & act & (r2 < P.rc2)) {
         const float rinv = __builtin_amdgcn_rsqf(r2);
         const float rinv2 = rinv * rinv;
         const float rinv3 = rinv2 * rinv;
         const float rinv6 = rinv3 * rinv3;
-        const float4 T = tabrow[tj];
+        const float4* tp = XSKIP<T_OUT, EL>
+                               ? reinterpret_cast<const float4*>(reinterpret_cast<const char*>(tabrow) + toff)
+                               : tabrow + (kj & 15u);
+        const float4 T = *tp;
         const float qq = I.q * qj;  // 3 q_i q_j when Q3
         const float C1 = fmaf(qq, Q3 ? P.crf1_3 : P.crf1, T.z);
         const float G6 = fmaf(T.x, rinv6, T.y);
@@ -219,7 +245,7 @@ __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const 
                 az = fmaf(g, dz, az);
             }
             if (WANTE) {
-                const float4 T2 = tabrow[ntab + tj];
+                const float4 T2 = tp[ntab];
                 if (EL == 0) r = r2 * rinv;
                 float e = fmaf(T2.z, rinv6, -T2.w) * rinv6;
                 const float eel = EL == 0 ? fmaf(P.crf1, r, (fmaf(P.krf, r2, rinv) - P.crf) + P.e0rf)
@@ -284,11 +310,12 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
                                           char* __restrict__ ws, int outsel, int energy_bead,
                                           int lists, int bead0, int p, int gw, const float4* s_tab,
                                           float* ring) {
-    using FL = Fields<MODE, N3>;
-    constexpr int NF = FL::NF, FV = FL::V;
+    using FL = Fields<MODE, N3, EL>;
+    constexpr int NF = FL::NF, FV = FL::V, FK = FL::K;
     int* clist = reinterpret_cast<int*>(ring) + NF * RING;
     int* slist = clist + CLIST + 16;
     unsigned long long* smask = reinterpret_cast<unsigned long long*>(slist + SLOTS);
+    unsigned* xmap = reinterpret_cast<unsigned*>(slist + SLOTS) + 16;
     const SegDev* __restrict__ sg = segs + p;
     const int nt = sg->s.nt;
     const int lane = threadIdx.x & 63;
@@ -326,9 +353,10 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
     P.krf2_3 = sg->s.krf2 * (1.0f / 3.0f);
     P.crf1_3 = sg->s.crf1 * (1.0f / 3.0f);
     // a scalar operand would halve the rate of the instructions that read it
-    if (MODE == 0) asm("" : "+v"(P.krf2), "+v"(P.crf1));
+    if (MODE == 0 && !ENERGY) asm("" : "+v"(P.krf2), "+v"(P.crf1));
     constexpr float QSC = THREE_Q<MODE, N3, EL> ? 3.0f : 1.0f;
-    const float sx = P.sx, sy = P.sy, sz = P.sz;
+    float sx = P.sx, sy = P.sy, sz = P.sz;
+    if (MODE == 0 && !ENERGY) asm("" : "+v"(sx), "+v"(sy), "+v"(sz));  // as above
     const float rcs = sg->s.rcs, rcs2 = sg->s.rcs2;
 
     // ---- the i-cluster ------------------------------------------------------------
@@ -459,17 +487,17 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
         const float qj = __uint_as_float(uj.w);
         if (exact) {
             if (wantE)
-                pair_term<MODE, true, true, false, EL>(I, P, tabrow, ntab, jx, jy, jz, qj, (uint32_t)mj.x, vjx,
+                pair_term<MODE, true, true, false, EL, false, true>(I, P, tabrow, ntab, jx, jy, jz, qj, 0u, (uint32_t)mj.x, vjx,
                                             vjy, vjz, vj, ax, ay, az, tx, ty, tz, en);
             else
-                pair_term<MODE, true, false, false, EL>(I, P, tabrow, ntab, jx, jy, jz, qj, (uint32_t)mj.x, vjx,
+                pair_term<MODE, true, false, false, EL, false, true>(I, P, tabrow, ntab, jx, jy, jz, qj, 0u, (uint32_t)mj.x, vjx,
                                              vjy, vjz, vj, ax, ay, az, tx, ty, tz, en);
         } else {
             if (wantE)
-                pair_term<MODE, false, true, false, EL>(I, P, tabrow, ntab, jx, jy, jz, qj, (uint32_t)mj.x, vjx,
+                pair_term<MODE, false, true, false, EL, false, true>(I, P, tabrow, ntab, jx, jy, jz, qj, 0u, (uint32_t)mj.x, vjx,
                                              vjy, vjz, vj, ax, ay, az, tx, ty, tz, en);
             else
-                pair_term<MODE, false, false, false, EL>(I, P, tabrow, ntab, jx, jy, jz, qj, (uint32_t)mj.x, vjx,
+                pair_term<MODE, false, false, false, EL, false, true>(I, P, tabrow, ntab, jx, jy, jz, qj, 0u, (uint32_t)mj.x, vjx,
                                               vjy, vjz, vj, ax, ay, az, tx, ty, tz, en);
         }
         eacc += 0.5f * en;
@@ -478,14 +506,15 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
     // ---- 8 j-atoms x 8 i-atoms per step from ring entries [0, count) ----------------
     // Every field of every step is one immediate offset from the same address.  Entries
     // past the count of a partial batch are zero.
-    auto eval_t = [&]<bool EX, bool WE, bool FULL>(int count) __attribute__((always_inline)) {
+    // EXCL: the batch may hold excluded partners.
+    auto eval_t = [&]<bool EX, bool WE, bool FULL, bool EXCL>(int count) __attribute__((always_inline)) {
         float* rb = ring + jslot;
         const int nsteps = FULL ? EB / 8 : (count + 7) >> 3;
 #pragma unroll
         for (int s = 0; s < nsteps; ++s) {
             const int o = s * 8;
             float jx, jy, jz, qj, vjx = 0.f, vjy = 0.f, vjz = 0.f;
-            uint32_t kj;
+            uint32_t kj = 0u, toff = 0u;
             if (N3) {
                 jx = rb[F_X * RING + o];
                 jy = rb[F_Y * RING + o];
@@ -509,17 +538,19 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
                 if (MODE == 1) {
                     v4f w = *reinterpret_cast<const v4f*>(ring4 + RING + o + jslot);
                     asm volatile("" : "+v"(w));
-                    kj = __float_as_uint(w[0]);
+                    toff = kj = __float_as_uint(w[0]);
                     vjx = w[1];
                     vjy = w[2];
                     vjz = w[3];
                 } else {
-                    kj = __float_as_uint(ring[4 * RING + o + jslot]);
+                    toff = kj = __float_as_uint(ring[4 * RING + o + jslot]);
                 }
+                if (XSKIP<N3, EL> && EXCL) kj = __float_as_uint(ring[FK * RING + o + jslot]);
             }
             const bool valid = FULL || o + jslot < count;
             float tx, ty, tz, en = 0.f;
-            pair_term<MODE, EX, WE, N3 == 1, EL, THREE_Q<MODE, N3, EL>>(I, P, tabrow, ntab, jx, jy, jz, qj, kj, vjx, vjy,
+            pair_term<MODE, EX, WE, N3 == 1, EL, THREE_Q<MODE, N3, EL>, EXCL>(
+                I, P, tabrow, ntab, jx, jy, jz, qj, toff, kj, vjx, vjy,
                                              vjz, valid, ax, ay, az, tx, ty, tz, en,
                                              ENERGY && FULL && s == 0);
             if (WE) eacc += N3 ? en : 0.5f * en;
@@ -558,28 +589,39 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
             }
         }
     };
-    auto eval = [&]<bool FULL>(int count) __attribute__((always_inline)) {
+    auto eval_x = [&]<bool FULL, bool EXCL>(int count) __attribute__((always_inline)) {
         if (exact) {
-            if (wantE) eval_t.template operator()<true, true, FULL>(count);
-            else eval_t.template operator()<true, false, FULL>(count);
+            if (wantE) eval_t.template operator()<true, true, FULL, EXCL>(count);
+            else eval_t.template operator()<true, false, FULL, EXCL>(count);
         } else {
-            if (wantE) eval_t.template operator()<false, true, FULL>(count);
-            else eval_t.template operator()<false, false, FULL>(count);
+            if (wantE) eval_t.template operator()<false, true, FULL, EXCL>(count);
+            else eval_t.template operator()<false, false, FULL, EXCL>(count);
         }
+    };
+    auto eval = [&](bool excl) __attribute__((always_inline)) {
+        if (!XSKIP<N3, EL> || excl) eval_x.template operator()<true, true>(64);
+        else eval_x.template operator()<true, false>(64);
     };
 
     // ---- the batch of listed slots in flight ----------------------------------------
     // gather() starts the loads of the next n (<= 64) listed atoms, one per lane;
     // to_ring() converts them and writes them to the ring.
-    int gs = 0, gk = 0;
+    const bool flags = XSKIP<N3, EL> && S < XSLOT && sg->s.nkey > 0;
+    const int slot_bits = flags ? XSLOT - 1 : ~0;
+    int gs = 0;
+    bool gx = false;  // the batch may hold excluded partners
+    int2 gk = make_int2(0, 0);
     uint4 gu = make_uint4(0u, 0u, 0u, 0u);
     float4 gv = make_float4(0.f, 0.f, 0.f, 0.f);
     auto gather = [&](int n) __attribute__((always_inline)) {
         const int sl = slist[(rp & (SLOTS - 1)) + lane];
         gs = lane < n ? sl : 0;  // lanes past the list load slot 0 (always present)
+        gx = !flags || __builtin_amdgcn_ballot_w64((gs & XSLOT) != 0) != 0ull;
+        gs &= slot_bits;
         gu = upos[(uint32_t)gs];
         if (MODE == 1) gv = vs[(uint32_t)gs];  // .w: the packed key
-        else gk = umeta[(uint32_t)gs].x;
+        else if (XSKIP<N3, EL>) gk = umeta[(uint32_t)gs];
+        else gk.x = umeta[(uint32_t)gs].x;
     };
     auto to_ring = [&](int n) __attribute__((always_inline)) {
         float jx, jy, jz;
@@ -593,7 +635,9 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
             jz = (float)(int)(gu.z - ucz) * sz;
         }
         float jq = QSC * __uint_as_float(gu.w);
-        float jk = MODE == 1 ? gv.w : __int_as_float(gk);
+        float jk = MODE == 1 ? gv.w : __int_as_float(gk.x);
+        float jt = jk;  // the entry's word
+        if (XSKIP<N3, EL>) jt = __int_as_float(MODE == 1 ? (__float_as_int(gv.w) & 15) << 4 : gk.y << 4);
         float vx = gv.x, vy = gv.y, vz = gv.z;
         if (n < 64) {
             const bool v = lane < n;
@@ -602,6 +646,7 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
             jz = v ? jz : 0.0f;
             jq = v ? jq : 0.0f;
             jk = v ? jk : 0.0f;
+            jt = v ? jt : 0.0f;
             vx = v ? vx : 0.0f;
             vy = v ? vy : 0.0f;
             vz = v ? vz : 0.0f;
@@ -624,8 +669,9 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
             }
         } else {
             ring4[lane] = make_float4(jx, jy, jz, jq);
-            if (MODE == 1) ring4[RING + lane] = make_float4(jk, vx, vy, vz);
-            else ring[4 * RING + lane] = jk;
+            if (MODE == 1) ring4[RING + lane] = make_float4(jt, vx, vy, vz);
+            else ring[4 * RING + lane] = jt;
+            if (XSKIP<N3, EL>) ring[FK * RING + lane] = jk;
         }
     };
 
@@ -649,10 +695,11 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
     int cur = 0;  // entries of the batch in flight
     auto batch = [&]() __attribute__((always_inline)) {
         if (cur > 0) to_ring(64);
+        const bool x = gx;
         gather(64);
         rp += 64;
         wave_sync();
-        if (cur > 0) eval.template operator()<true>(64);
+        if (cur > 0) eval(x);
         wave_sync();  // reads of the ring are done before it is overwritten
         cur = 64;
     };
@@ -685,14 +732,28 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
 
     // ---- search ---------------------------------------------------------------------
     // State: clusters [tq, T) of clist still to test.
-    const int wx = sg->s.wx, wy = sg->s.wy, nst = searched ? wx * wy : 0;
+    const int lst = sg->s.nst, nst = !searched ? 0 : lst > 0 ? lst : sg->s.wx * sg->s.wy;
     int k0 = 0, skip = 0, T = 0, tq = 0;
+    if (flags && nst > 0) {
+        // excluded partners: key differences of up to 2; lane 8 i + j looks up the j-th of
+        // atom i (j < 4), lane 4 the cluster itself
+        reinterpret_cast<uint2*>(xmap)[lane] = make_uint2(0u, 0u);
+        const int k = (mi.x >> 4) + (jslot < 2 ? jslot - 2 : jslot - 1);
+        int cl = lane == 4 ? c : -1;
+        if (I.v && jslot < 4 && k >= 0 && k < sg->s.nkey) {
+            const int a = sg->s.kmap[k];
+            if (a >= 0) cl = wsp<const int>(ws, sg->o_slotof)[(size_t)b * sg->s.Q + a] >> 3;
+        }
+        wave_sync();
+        if (cl >= 0) atomicOr(xmap + ((cl >> 5) & (XMAP - 1)), 1u << (cl & 31));
+        wave_sync();
+    }
     uint4 nu = make_uint4(0u, 0u, 0u, 0u);
     int nslot = 0;
     // Positions of the chunk of 8 candidate clusters at clist[q] (one chunk ahead of use).
     auto load_chunk = [&](int q) __attribute__((always_inline)) {
         nslot = (clist[q + sub] << 3) | atom;
-        nu = upos[(uint32_t)nslot];
+        nu = upos[(uint32_t)(nslot & slot_bits)];
     };
     // Cluster ranges [a0, a1) and [b0, b1) of stencil column k of this lane (empty past the
     // stencil).  Everything derived from the box is computed here, on its own copy of the
@@ -738,11 +799,17 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
         const uint4 ref = upos[c * CLUSTER + 3];
         const int cx = fixed_bin(ref.x, ncx), cy = fixed_bin(ref.y, ncy);
         if (k < nst) {
-            const int ox = k / wy, oy = k - ox * wy;
             // stencil half widths are below the column counts (else the stencil spans
             // every column), so one wrap suffices
-            int jxc = sg->s.allx ? ox : cx + ox - sg->s.rx;
-            int jyc = sg->s.ally ? oy : cy + oy - sg->s.ry;
+            int jxc, jyc;
+            if (lst > 0) {
+                jxc = cx + sg->s.st[k][0];
+                jyc = cy + sg->s.st[k][1];
+            } else {
+                const int wy = sg->s.wy, ox = k / wy, oy = k - ox * wy;
+                jxc = sg->s.allx ? ox : cx + ox - sg->s.rx;
+                jyc = sg->s.ally ? oy : cy + oy - sg->s.ry;
+            }
             jxc += jxc < 0 ? ncx : (jxc >= ncx ? -ncx : 0);
             jyc += jyc < 0 ? ncy : (jyc >= ncy ? -ncy : 0);
             float dxc = ((float)jxc + 0.5f) * cwx - xref;
@@ -801,7 +868,28 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
             const int at = incl - len - skip;  // list position of this column's first cluster
             const int t1 = min(len, T - at);
             wave_sync();  // the previous list has been consumed
-            for (int t = max(0, -at); t < t1; ++t) clist[at + t] = t < la ? a0 + t : b0 + (t - la);
+            // Each cluster range marks its first list position with its number (2 lane, the
+            // second range of a column 2 lane + 1; ranges follow one another in that order);
+            // a running maximum over the positions then gives the range of each, and the
+            // clusters of a range are consecutive.  The marks' bases wait in the ring, which
+            // holds no batch here.
+            int* base = reinterpret_cast<int*>(ring);
+            reinterpret_cast<int4*>(clist)[lane] = make_int4(0, 0, 0, 0);
+            wave_sync();
+            base[2 * lane] = a0 - at;
+            base[2 * lane + 1] = b0 - at - la;
+            if (la > 0 && at + la > 0 && at < T) clist[max(at, 0)] = 2 * lane;
+            if (len > la && at + len > 0 && at + la < T) clist[max(at + la, 0)] = 2 * lane + 1;
+            wave_sync();
+            int last = 0;
+            for (int g = 0; g < T; g += 64) {
+                const int own = max(wave_incl_max(clist[g + lane]), last);
+                last = __builtin_amdgcn_readlane(own, 63);
+                int cl = base[own] + g + lane;
+                if (flags && (xmap[(cl >> 5) & (XMAP - 1)] >> (cl & 31)) & 1u) cl |= XFLAG;
+                clist[g + lane] = cl;
+            }
+            wave_sync();
             skip += T;
             if (skip >= total) {
                 k0 += 64;
@@ -863,9 +951,10 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
         const int n = wp - rp;
         if (cur > 0) {
             to_ring(64);
+            const bool x = gx;
             if (n > 0) gather(n);
             wave_sync();
-            eval.template operator()<true>(64);
+            eval(x);
             wave_sync();
         } else if (n > 0) {
             gather(n);
@@ -873,7 +962,7 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
         if (n > 0) {
             to_ring(n);
             wave_sync();
-            eval.template operator()<false>(n);
+            eval_x.template operator()<false, true>(n);
         }
     }
     if (rec && lane == 0) *nlc = wr;
@@ -931,7 +1020,6 @@ template <int MODE, int PW, int N3, int EL, int WE>
 __global__ void __launch_bounds__(64 * PW, (PAIR_WAVES<MODE, N3, EL, WE>))
     k_pair(const SegDev* __restrict__ segs, Launch L, char* __restrict__ ws, int outsel,
            int energy_bead, int lists, int bead0) {
-    constexpr int NF = Fields<MODE, N3>::NF;
     extern __shared__ float4 s_dyn[];
     const int nblk = L.pf[L.nseg];
     const int per = (nblk + 7) >> 3;
@@ -944,7 +1032,7 @@ __global__ void __launch_bounds__(64 * PW, (PAIR_WAVES<MODE, N3, EL, WE>))
     __syncthreads();  // the only block barrier: waves are independent from here on
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar indices
     pair_wave<MODE, N3, EL, WE>(segs, L, ws, outsel, energy_bead, lists, bead0, p,
-                                (lblk - L.pf[p]) * PW + wave, s_tab, s_ring + wave * WAVE_LDS<NF>);
+                                (lblk - L.pf[p]) * PW + wave, s_tab, s_ring + wave * WAVE_LDS<Fields<MODE, N3, EL>>);
 }
 
 // Persistent form: as many workgroups as the GPU holds at once, each taking logical blocks
@@ -959,7 +1047,6 @@ template <int MODE, int PW, int N3, int EL, int WE>
 __global__ void __launch_bounds__(64 * PW, (PAIR_WAVES<MODE, N3, EL, WE>))
     k_pair_q(const SegDev* __restrict__ segs, Launch L, char* __restrict__ ws, int outsel,
              int energy_bead, int lists, int bead0, int* __restrict__ queue) {
-    constexpr int NF = Fields<MODE, N3>::NF;
     extern __shared__ float4 s_dyn[];
     __shared__ int s_next[2];
     const int nblk = L.pf[L.nseg];
@@ -982,7 +1069,7 @@ __global__ void __launch_bounds__(64 * PW, (PAIR_WAVES<MODE, N3, EL, WE>))
             cur = p;
         }
         pair_wave<MODE, N3, EL, WE>(segs, L, ws, outsel, energy_bead, lists, bead0, p,
-                                    (lblk - L.pf[p]) * PW + wave, s_tab, s_ring + wave * WAVE_LDS<NF>);
+                                    (lblk - L.pf[p]) * PW + wave, s_tab, s_ring + wave * WAVE_LDS<Fields<MODE, N3, EL>>);
     }
 }
 
@@ -1027,7 +1114,7 @@ static void launch_pair_t(const SegDev* dsegs, const SegDev* hsegs, const Launch
     const int nblk = L.pf[base.nseg];
     if (nblk == 0) return;
     const size_t tab = TAB_COPIES<MODE> * (size_t)L.ntmax * L.ntmax * sizeof(float4);
-    const size_t wlds = (size_t)WAVE_LDS<Fields<MODE, N3>::NF> * sizeof(float);
+    const size_t wlds = (size_t)WAVE_LDS<Fields<MODE, N3, EL>> * sizeof(float);
     if (persistent) {
         // a grid of what the GPU holds at once: a multiple of 8 workgroups (one set per XCD
         // queue), no more workgroups than logical blocks

@@ -352,6 +352,26 @@ static SysDev plan_geometry(const mop_system_s* sys, const mop_plan_opts* opts) 
     s.ally = s.wy >= s.ncy;
     if (s.allx) s.wx = s.ncx;
     if (s.ally) s.wy = s.ncy;
+    // Columns of the square stencil that no atom of the centre column can reach (corners) are
+    // left out when the rest fits one column per lane: 61 of 81 for a 1.2 nm cutoff and 0.4
+    // nm columns, one pass of the search's column step instead of two.  The 0.001 nm more
+    // than cover what displacements of a kept binning and rounding could add.
+    s.nst = 0;
+    if (!s.allx && !s.ally && s.rx < 128 && s.ry < 128) {
+        int n = 0;
+        const double reach = rcs + 1.0e-3;
+        for (int ox = -s.rx; ox <= s.rx; ++ox)
+            for (int oy = -s.ry; oy <= s.ry; ++oy) {
+                const double gx = std::max(0, std::abs(ox) - 1) * cwx, gy = std::max(0, std::abs(oy) - 1) * cwy;
+                if (gx * gx + gy * gy >= reach * reach) continue;
+                if (n < STENCIL) {
+                    s.st[n][0] = (signed char)ox;
+                    s.st[n][1] = (signed char)oy;
+                }
+                ++n;
+            }
+        if (n <= STENCIL) s.nst = n;
+    }
     s.S = ((s.Q + 7 * s.ncol) + 7) & ~7;
     s.cpb = s.S / CLUSTER;
     for (int a = 0; a < 3; ++a) {
@@ -616,6 +636,14 @@ int mop_system_create(mop_ctx ctx, const mop_system_desc* d, mop_system* out) {
     s.nbond_entries = 2 * d->nbonds;
     int e = 0;
     if (!e) e = upload(sys, qs.data(), Q, &s.qs);
+    std::vector<int> kmap(*std::max_element(key.begin(), key.end()) + 1, -1);
+    bool one_each = true;  // explicit positions may repeat inside a molecule
+    for (int i = 0; i < Q; ++i) {
+        one_each = one_each && kmap[key[i]] < 0;
+        kmap[key[i]] = i;
+    }
+    s.nkey = one_each ? (int)kmap.size() : 0;
+    if (!e) e = upload(sys, kmap.data(), kmap.size(), &s.kmap);
     for (int i = 0; i < Q; ++i) key[i] = key[i] * 16 + typ[i];  // type < MAXTYPES = 16
     if (!e) e = upload(sys, key.data(), Q, &s.key);
     if (!e) e = upload(sys, typ.data(), Q, &s.type);

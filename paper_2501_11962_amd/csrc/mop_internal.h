@@ -14,7 +14,8 @@
 //   Per atom (original order): slotof, pair force / pair HVP outputs (float4).
 //   Per cluster: the neighbour list a force pass records for the Hessian pass of the
 //     same bead (nl: int [lcap] records, one per candidate cluster with atoms that passed
-//     the search, in search order: cluster index << 8 | 8-bit mask of those atoms; nlc:
+//     the search, in search order: flag << 31 (the cluster may hold excluded partners)
+//     | cluster index << 8 | 8-bit mask of those atoms; nlc:
 //     their count, which may exceed lcap, then the list is incomplete).
 // Per path: FP64 residuals d^n [(N-1)][Q][3], reduction partials, per-bead max |d|^2.
 // Particle-mesh Ewald (systems with Ewald electrostatics), per pair bead:
@@ -45,6 +46,7 @@ constexpr int CLUSTER = 8;        // atoms per cluster
 constexpr int RING = 64;          // j-atom ring per wave: one evaluation batch
 constexpr int CLIST = 256;        // candidate-cluster list per wave
 constexpr int MAXTYPES = 16;      // LJ types (the type fills the low 4 bits of a packed key)
+constexpr int STENCIL = 64;       // listed stencil columns at most (one per lane)
 constexpr int EWB = 256;          // block size of the elementwise kernels
 constexpr int WAVES_PERSISTENT = 0x100;  // or-ed into a plan's waves: persistent pair launches
 constexpr size_t WS_QUEUE = 64;   // workspace byte offset of the 8 work-queue counters
@@ -69,6 +71,8 @@ struct SysDev {
     int allx, ally;   // 1: the column stencil spans every column along that axis
     int rx, ry;       // stencil half widths (columns) when not spanning
     int wx, wy;       // stencil widths (columns)
+    int nst;          // stencil columns within reach, listed in st (0: all wx * wy)
+    signed char st[STENCIL][2];  // x and y offsets, in the order of the full stencil
     int nbond_entries;
     double L[3];
     float sc[3];      // nm per fixed-point unit: L / 2^32
@@ -87,6 +91,8 @@ struct SysDev {
     const float* qs;      // [Q] charge * sqrt(f / eps_r)
     const int* key;       // [Q] 16 * exclusion key + LJ type; excluded pairs: |key_i - key_j| <= 2
     const int* type;      // [Q]
+    const int* kmap;      // [nkey] atom of an exclusion key, -1: none
+    int nkey;             // 0: keys repeat, no such map
     const double* c;      // [Q] dt / (m nu)
     const double* K;      // [Q] m nu / (2 dt)
     const double* minv;   // [Q] 1 / m (path dynamics)
