@@ -2,7 +2,10 @@
 // S = s(R^N) - s(R^1), with s the distance between the centres of mass of atom groups A
 // and B (section 3: ligand and binding pocket), and a Gaussian bias V(S) on it.
 //
-// One block per call (the groups are small):
+// One block per call (the groups are small), bound by the latency of its steps: each wave
+// sums a sixteenth of the atoms of one (bead, group) pair, so that all moments meet at one
+// barrier and the Gaussians at a second (block-wide sums one after another, two barriers
+// each, took 17 us for groups of 8 and 187 atoms).
 //   1. centres of mass of A and B in beads 1 and N, each from the minimum-image offsets to
 //      the group's first atom, FP64 block sums;
 //   2. V(S) and dV/dS over the deposited Gaussians, FP64 block sums;
@@ -17,24 +20,9 @@ namespace mop {
 
 namespace {
 
-constexpr int BIAS_THREADS = 256;
-
-// Sums m_i mi(x_i - x_ref) over a group (3 components) and the group mass.
-__device__ void group_moment(const double* X, const int* idx, int n, const double* minv,
-                             const double L[3], double* sh, double out[4]) {
-    const double* xr = X + 3 * (size_t)idx[0];
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int k = threadIdx.x; k < n; k += BIAS_THREADS) {
-        const int i = idx[k];
-        const double m = 1.0 / minv[i];
-        for (int a = 0; a < 3; ++a) acc[a] += m * min_img(X[3 * (size_t)i + a] - xr[a], L[a]);
-        acc[3] += m;
-    }
-    for (int a = 0; a < 4; ++a) {
-        const double t = block_sum(acc[a], sh);
-        if (threadIdx.x == 0) out[a] = t;
-    }
-}
+constexpr int BIAS_THREADS = 1024;
+constexpr int BIAS_WAVES = BIAS_THREADS / 64;
+constexpr int PARTS = BIAS_WAVES / 4;  // waves per (bead, group) pair
 
 }  // namespace
 
@@ -42,26 +30,46 @@ __global__ void __launch_bounds__(BIAS_THREADS) k_bias(BiasDev bd, const double*
                                                        int N, int Q, double* __restrict__ G,
                                                        double* __restrict__ out, int deposit,
                                                        int* __restrict__ status) {
-    __shared__ double sh[BIAS_THREADS / 64];
-    __shared__ double mom[4][4];    // [bead 1 A, bead 1 B, bead N A, bead N B][x, y, z, M]
-    __shared__ double res[8];       // e1 (3), eN (3), dV/dS, V
+    // sums m_i mi(x_i - x_ref) (3 components) and group mass, a part per wave: [bead 1 A,
+    // bead 1 B, bead N A, bead N B][part][x, y, z, M]
+    __shared__ double mom[4][PARTS][4];
+    __shared__ double gauss[BIAS_WAVES][2];  // V and dV/dS, a part per wave
     const double* R1 = R;
     const double* RN = R + (size_t)(N - 1) * Q * 3;
-    group_moment(R1, bd.A, bd.nA, bd.minv, bd.L, sh, mom[0]);
-    group_moment(R1, bd.B, bd.nB, bd.minv, bd.L, sh, mom[1]);
-    group_moment(RN, bd.A, bd.nA, bd.minv, bd.L, sh, mom[2]);
-    group_moment(RN, bd.B, bd.nB, bd.minv, bd.L, sh, mom[3]);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ng = *bd.count;
+    {
+        const int pair = wave & 3, part = wave >> 2;
+        const double* X = pair < 2 ? R1 : RN;
+        const int* idx = pair & 1 ? bd.B : bd.A;
+        const int n = pair & 1 ? bd.nB : bd.nA;
+        const double* xr = X + 3 * (size_t)idx[0];
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int k = part * 64 + lane; k < n; k += PARTS * 64) {
+            const int i = idx[k];
+            const double m = 1.0 / bd.minv[i];
+            for (int a = 0; a < 3; ++a) acc[a] += m * min_img(X[3 * (size_t)i + a] - xr[a], bd.L[a]);
+            acc[3] += m;
+        }
+        for (int a = 0; a < 4; ++a) {
+            const double t = wave_sum(acc[a]);
+            if (lane == 0) mom[pair][part][a] = t;
+        }
+    }
     __syncthreads();
+    auto moment = [&](int pair, int a) {
+        double t = mom[pair][0][a];
+        for (int k = 1; k < PARTS; ++k) t += mom[pair][k][a];
+        return t;
+    };
     // s and e for bead 1 (k = 0) and bead N (k = 1), computed redundantly by every thread
     double s[2], e[2][3];
     for (int k = 0; k < 2; ++k) {
         const double* X = k == 0 ? R1 : RN;
-        const double* ma = mom[2 * k];
-        const double* mb = mom[2 * k + 1];
         double d2 = 0.0, d[3];
         for (int a = 0; a < 3; ++a) {
-            const double ca = X[3 * (size_t)bd.A[0] + a] + ma[a] / ma[3];
-            const double cb = X[3 * (size_t)bd.B[0] + a] + mb[a] / mb[3];
+            const double ca = X[3 * (size_t)bd.A[0] + a] + moment(2 * k, a) / moment(2 * k, 3);
+            const double cb = X[3 * (size_t)bd.B[0] + a] + moment(2 * k + 1, a) / moment(2 * k + 1, 3);
             d[a] = min_img(cb - ca, bd.L[a]);
             d2 += d[a] * d[a];
         }
@@ -70,7 +78,6 @@ __global__ void __launch_bounds__(BIAS_THREADS) k_bias(BiasDev bd, const double*
     }
     const double S = s[1] - s[0];
     // V(S) and V'(S)
-    const int ng = *bd.count;
     double v = 0.0, dv = 0.0;
     const double is2 = 1.0 / (bd.sigma * bd.sigma);
     for (int k = threadIdx.x; k < ng; k += BIAS_THREADS) {
@@ -79,19 +86,23 @@ __global__ void __launch_bounds__(BIAS_THREADS) k_bias(BiasDev bd, const double*
         v += g;
         dv -= x * is2 * g;
     }
-    const double V = block_sum(v, sh);
-    const double dV = block_sum(dv, sh);
-    if (threadIdx.x == 0) {
-        res[6] = dV;
-        res[7] = V;
+    v = wave_sum(v);
+    dv = wave_sum(dv);
+    if (lane == 0) {
+        gauss[wave][0] = v;
+        gauss[wave][1] = dv;
     }
     __syncthreads();
-    const double dVs = res[6];
+    double Vb = 0.0, dVs = 0.0;
+    for (int k = 0; k < BIAS_WAVES; ++k) {
+        Vb += gauss[k][0];
+        dVs += gauss[k][1];
+    }
     // gradient: bead N gets +dV ds/dR^N, bead 1 gets -dV ds/dR^1
     if (G) {
         double* G1 = G;
         double* GN = G + (size_t)(N - 1) * Q * 3;
-        const double MA0 = mom[0][3], MB0 = mom[1][3];
+        const double MA0 = moment(0, 3), MB0 = moment(1, 3);
         for (int k = threadIdx.x; k < bd.nA; k += BIAS_THREADS) {
             const int i = bd.A[k];
             const double w = dVs / (bd.minv[i] * MA0);
@@ -110,7 +121,6 @@ __global__ void __launch_bounds__(BIAS_THREADS) k_bias(BiasDev bd, const double*
         }
     }
     if (threadIdx.x == 0) {
-        const double Vb = res[7];
         if (out) {
             out[0] = Vb;
             out[1] = S;
