@@ -6,6 +6,7 @@
 //               (kernels 4-6 as one gradient; F_eff = -G is eqs. 5-7), or with the
 //               finite-difference term [F(R+eps d) - F(R-eps d)]/(4 eps) of eq. (5)
 //               (kernels 2-3) in place of -1/2 H d.
+//               and, in a block of its own, V_eff.
 //   k_reduce_*  deterministic FP64 sums of the per-block partials.
 // All elementwise, HBM-bound; blocks never straddle beads (per-bead block counts).
 #include "device_common.h"
@@ -100,9 +101,76 @@ __global__ void __launch_bounds__(EWB) k_resid(const SegDev* __restrict__ segs, 
     }
 }
 
+// Sum of the per-cluster pair-energy partials of bead b (weights applied in the kernel).
+__device__ double pair_energy_of_bead(const SegDev& sg, char* ws, int b, int t0, int stride) {
+    const int ncol = sg.s.ncol;
+    const int nslots = wsp<const int>(ws, sg.o_colstart)[(size_t)b * (ncol + 1) + ncol];
+    const int ncl = nslots / CLUSTER;
+    const double* ep = wsp<const double>(ws, sg.o_epart) + (size_t)b * sg.s.cpb;
+    double e0 = 0.0, e1 = 0.0;
+    int c = t0;
+    for (; c + stride < ncl; c += 2 * stride) {  // two independent chains in flight
+        e0 += ep[c];
+        e1 += ep[c + stride];
+    }
+    if (c < ncl) e0 += ep[c];
+    return e0 + e1;
+}
+
+// This thread's share of the PME reciprocal energy of bead b (partials of the solve
+// kernel, already halved); 0 without PME.
+__device__ double pme_energy_of_bead(const SegDev& sg, char* ws, int b, int t0, int stride) {
+    if (sg.s.elec != 1) return 0.0;
+    const double* ep = wsp<const double>(ws, sg.o_pep) + (size_t)b * sg.s.nsb;
+    double e = 0.0;
+    for (int k = t0; k < sg.s.nsb; k += stride) e += ep[k];
+    return e;
+}
+
+// V_eff = U(R^1) + E_spring of path p, by one block of EWB threads.
+__device__ __forceinline__ void reduce_veff(const SegDev* __restrict__ segs, const Launch& L,
+                                            const CallPtrs& cp, int p, double* sh) {
+    const SegDev& sg = segs[p];
+    char* ws = cp.ws;
+    const int N = L.N[p];
+    const int nbr = N > 1 ? N - 1 : 1;
+    const double* rp = wsp<const double>(ws, sg.o_rpart);
+    double es = 0.0, eb = 0.0;
+    for (int k = threadIdx.x; k < nbr * sg.bpb; k += EWB) es += rp[2 * k];
+    for (int k = threadIdx.x; k < sg.bpb; k += EWB) eb += rp[2 * k + 1];
+    const double ep = pair_energy_of_bead(sg, ws, 0, threadIdx.x, EWB) +
+                      pme_energy_of_bead(sg, ws, 0, threadIdx.x, EWB);
+    const double S_es = block_sum(es, sh);
+    const double S_u = block_sum(eb + ep, sh) + (sg.s.elec == 1 ? sg.s.e_const : 0.0);
+    if (threadIdx.x == 0) {
+        double* er = wsp<double>(ws, sg.o_eres);
+        er[0] = S_u + S_es;
+        er[1] = S_u;
+        er[2] = S_es;
+        if (cp.veff) cp.veff[sg.vidx] = S_u + S_es;
+        if (cp.u1) cp.u1[sg.vidx] = S_u;
+        if (cp.espring) cp.espring[sg.vidx] = S_es;
+        if (!isfinite(S_u + S_es)) flag(cp.status, ST_NONFINITE);
+    }
+}
+
+__global__ void __launch_bounds__(EWB) k_reduce_veff(const SegDev* __restrict__ segs, Launch L,
+                                                     CallPtrs cp) {
+    __shared__ double sh[EWB / 64];
+    reduce_veff(segs, L, cp, blockIdx.x, sh);
+}
+
+// The first block of each path sums V_eff, which needs nothing from the others: a launch of
+// its own took 4 us on small systems (of 40 for 256 atoms x 32 beads) and 13 after the 63 us
+// of the assembly of 150,000 x 16.
 __global__ void __launch_bounds__(EWB) k_assemble(const SegDev* __restrict__ segs, Launch L,
                                                   CallPtrs cp, int fd) {
-    const int blk = blockIdx.x;
+    __shared__ double sh[EWB / 64];
+    const int blk = (int)blockIdx.x - L.nseg;
+    if (blk < 0) {
+        reduce_veff(segs, L, cp, blockIdx.x, sh);
+        return;
+    }
     const int p = find_seg(L, blk);
     const SegDev& sg = segs[p];
     const SysDev& s = sg.s;
@@ -156,75 +224,6 @@ __global__ void __launch_bounds__(EWB) k_assemble(const SegDev* __restrict__ seg
     G[1] = g[1];
     G[2] = g[2];
     if (!finite3(g[0], g[1], g[2])) flag(cp.status, ST_NONFINITE);
-}
-
-// Sum of the per-cluster pair-energy partials of bead b (weights applied in the kernel).
-__device__ double pair_energy_of_bead(const SegDev& sg, char* ws, int b, int t0, int stride) {
-    const int ncol = sg.s.ncol;
-    const int nslots = wsp<const int>(ws, sg.o_colstart)[(size_t)b * (ncol + 1) + ncol];
-    const int ncl = nslots / CLUSTER;
-    const double* ep = wsp<const double>(ws, sg.o_epart) + (size_t)b * sg.s.cpb;
-    double e0 = 0.0, e1 = 0.0;
-    int c = t0;
-    for (; c + stride < ncl; c += 2 * stride) {  // two independent chains in flight
-        e0 += ep[c];
-        e1 += ep[c + stride];
-    }
-    if (c < ncl) e0 += ep[c];
-    return e0 + e1;
-}
-
-// This thread's share of the PME reciprocal energy of bead b (partials of the solve
-// kernel, already halved); 0 without PME.
-__device__ double pme_energy_of_bead(const SegDev& sg, char* ws, int b, int t0, int stride) {
-    if (sg.s.elec != 1) return 0.0;
-    const double* ep = wsp<const double>(ws, sg.o_pep) + (size_t)b * sg.s.nsb;
-    double e = 0.0;
-    for (int k = t0; k < sg.s.nsb; k += stride) e += ep[k];
-    return e;
-}
-
-// Block-wide sum over RVB threads (result valid in thread 0).
-constexpr int RVB = 1024;
-__device__ __forceinline__ double block_sum_rvb(double v, double* sh) {
-    v = wave_sum(v);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    __syncthreads();
-    if (lane == 0) sh[w] = v;
-    __syncthreads();
-    double s = 0.0;
-    if (threadIdx.x == 0)
-        for (int k = 0; k < RVB / 64; ++k) s += sh[k];
-    return s;
-}
-
-// One block per path: V_eff = U(R^1) + E_spring.
-__global__ void __launch_bounds__(RVB) k_reduce_veff(const SegDev* __restrict__ segs, Launch L,
-                                                     CallPtrs cp) {
-    __shared__ double sh[RVB / 64];
-    const int p = blockIdx.x;
-    const SegDev& sg = segs[p];
-    char* ws = cp.ws;
-    const int N = L.N[p];
-    const int nbr = N > 1 ? N - 1 : 1;
-    const double* rp = wsp<const double>(ws, sg.o_rpart);
-    double es = 0.0, eb = 0.0;
-    for (int k = threadIdx.x; k < nbr * sg.bpb; k += RVB) es += rp[2 * k];
-    for (int k = threadIdx.x; k < sg.bpb; k += RVB) eb += rp[2 * k + 1];
-    const double ep = pair_energy_of_bead(sg, ws, 0, threadIdx.x, RVB) +
-                      pme_energy_of_bead(sg, ws, 0, threadIdx.x, RVB);
-    const double S_es = block_sum_rvb(es, sh);
-    const double S_u = block_sum_rvb(eb + ep, sh) + (sg.s.elec == 1 ? sg.s.e_const : 0.0);
-    if (threadIdx.x == 0) {
-        double* er = wsp<double>(ws, sg.o_eres);
-        er[0] = S_u + S_es;
-        er[1] = S_u;
-        er[2] = S_es;
-        if (cp.veff) cp.veff[sg.vidx] = S_u + S_es;
-        if (cp.u1) cp.u1[sg.vidx] = S_u;
-        if (cp.espring) cp.espring[sg.vidx] = S_es;
-        if (!isfinite(S_u + S_es)) flag(cp.status, ST_NONFINITE);
-    }
 }
 
 // bead_forces: F = F_pair + F_bond (FP64 sum, FP32 out); bond energies per block.
@@ -337,13 +336,13 @@ void run_resid(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, con
 void run_assemble(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, const CallPtrs& cp,
                   int fd, hipStream_t st) {
     const Launch L = per_bead_blocks(base, hsegs, false, true);
-    hipLaunchKernelGGL(k_assemble, dim3(L.pf[L.nseg]), dim3(EWB), 0, st, dsegs, L, cp, fd);
+    hipLaunchKernelGGL(k_assemble, dim3(L.nseg + L.pf[L.nseg]), dim3(EWB), 0, st, dsegs, L, cp, fd);
 }
 
 void run_reduce_veff(const SegDev* dsegs, const SegDev* hsegs, const Launch& base,
                      const CallPtrs& cp, hipStream_t st) {
     (void)hsegs;
-    hipLaunchKernelGGL(k_reduce_veff, dim3(base.nseg), dim3(RVB), 0, st, dsegs, base, cp);
+    hipLaunchKernelGGL(k_reduce_veff, dim3(base.nseg), dim3(EWB), 0, st, dsegs, base, cp);
 }
 
 void run_finalize_forces(const SegDev* dsegs, const SegDev* hsegs, const Launch& base,

@@ -28,8 +28,10 @@ void run_pair(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char
 // FP64 path kernels.
 void run_resid(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, const CallPtrs& cp,
                int want_dmax, hipStream_t st);
+// Gradient and V_eff.
 void run_assemble(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, const CallPtrs& cp,
                   int fd, hipStream_t st);
+// V_eff alone.
 void run_reduce_veff(const SegDev* dsegs, const SegDev* hsegs, const Launch& base,
                      const CallPtrs& cp, hipStream_t st);
 // bead_forces / bead_hvp finishing kernels.

@@ -1060,8 +1060,8 @@ static void path_sequence(const SegDev* dsegs, const SegDev* hsegs, const Launch
         mark(5);
         mark(6);
         mark(7);
+        run_reduce_veff(dsegs, hsegs, base, cp, st);
     }
-    run_reduce_veff(dsegs, hsegs, base, cp, st);
     mark(8);
 }
 
