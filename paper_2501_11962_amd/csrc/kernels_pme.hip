@@ -261,6 +261,70 @@ __global__ void __launch_bounds__(EWB) k_pme_tile_scatter(const SegDev* __restri
     wsp<double4>(ws, sg.o_ptw)[slot] = make_double4(w[0], w[1], w[2], s.qd[i]);
 }
 
+// The tile order of a bead with few atoms in one workgroup (counts in LDS, atoms in
+// registers): on small systems the four kernels above are launches and trips through memory
+// at the head of the mesh work, which bounds those systems.  Atoms of a tile come in any order
+// here as there: the spread sums integers and the gather treats each atom alone.
+constexpr int SORT_BLOCK = 1024;
+constexpr int SORT_J = 4;               // atoms per thread
+constexpr int SORT_TILES = 12288;       // tiles at most (48 KB of counts)
+
+__global__ void __launch_bounds__(SORT_BLOCK) k_pme_tile_sort(const SegDev* __restrict__ segs, char* ws,
+                                                              const double* __restrict__ R, int fdsign,
+                                                              double fdh) {
+    extern __shared__ int cnt[];
+    __shared__ int wsum[SORT_BLOCK / 64];
+    const SegDev& sg = segs[0];
+    const SysDev& s = sg.s;
+    const int b = blockIdx.x, tid = threadIdx.x, nt = s.ntile;
+    const int lane = tid & 63, wv = tid >> 6;
+    for (int t = tid; t < nt; t += SORT_BLOCK) cnt[t] = 0;
+    __syncthreads();
+    int bse[SORT_J][3], tile[SORT_J], rank[SORT_J];
+    double w[SORT_J][3];
+#pragma unroll
+    for (int j = 0; j < SORT_J; ++j) {
+        const int i = tid + j * SORT_BLOCK;
+        if (i < s.Q) {
+            double x[3];
+            atom_pos(sg, ws, R, b, i, fdsign, fdh, x);
+            grid_base(s, x, bse[j], w[j]);
+            tile[j] = (s.tile_of[s.tof_off[0] + bse[j][0]] * s.ntl[1] + s.tile_of[s.tof_off[1] + bse[j][1]]) *
+                          s.ntl[2] +
+                      s.tile_of[s.tof_off[2] + bse[j][2]];
+            rank[j] = atomicAdd(cnt + tile[j], 1);
+        }
+    }
+    __syncthreads();
+    int* start = wsp<int>(ws, sg.o_pts) + (size_t)b * (nt + 1);
+    int carry = 0;
+    for (int base = 0; base < nt; base += SORT_BLOCK) {
+        const int k = base + tid;
+        const int v = k < nt ? cnt[k] : 0;
+        const int incl = wave_incl_scan(v);
+        if (lane == 63) wsum[wv] = incl;
+        __syncthreads();
+        int off = carry;
+        for (int u = 0; u < wv; ++u) off += wsum[u];
+        if (k < nt) {
+            cnt[k] = off + incl - v;
+            start[k] = off + incl - v;
+        }
+        for (int u = 0; u < SORT_BLOCK / 64; ++u) carry += wsum[u];
+        __syncthreads();
+    }
+    if (tid == 0) start[nt] = carry;
+#pragma unroll
+    for (int j = 0; j < SORT_J; ++j) {
+        const int i = tid + j * SORT_BLOCK;
+        if (i < s.Q) {
+            const size_t slot = (size_t)b * s.Q + cnt[tile[j]] + rank[j];
+            wsp<int4>(ws, sg.o_ptb)[slot] = make_int4(bse[j][0], bse[j][1], bse[j][2], i);
+            wsp<double4>(ws, sg.o_ptw)[slot] = make_double4(w[j][0], w[j][1], w[j][2], s.qd[i]);
+        }
+    }
+}
+
 // One workgroup per (bead, tile): KIND 0 charges of R (displaced with fdsign), KIND 1
 // dipoles q_i v_i (V: [nb][Q][3]).  Beads nb .. nbatch-1 of the FFT batch get zeros.
 constexpr int SPREAD_CAP = 1024;  // candidate list of the spreading kernel (LDS)
@@ -621,6 +685,12 @@ void gather_p(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const doub
 
 void run_pme_sort(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* R,
                   int fdsign, double fdh, hipStream_t st) {
+    // few atoms per bead: see k_pme_tile_sort
+    if (h.s.Q <= SORT_BLOCK * SORT_J && h.s.ntile <= SORT_TILES) {
+        hipLaunchKernelGGL(k_pme_tile_sort, dim3(nb), dim3(SORT_BLOCK), (size_t)h.s.ntile * sizeof(int), st,
+                           dsegs, ws, R, fdsign, fdh);
+        return;
+    }
     const int n = nb * h.s.ntile;
     hipLaunchKernelGGL(k_pme_tile_zero, dim3((n + PME_BLOCK - 1) / PME_BLOCK), dim3(PME_BLOCK), 0, st,
                        dsegs, n, ws);
