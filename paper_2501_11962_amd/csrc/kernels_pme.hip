@@ -527,107 +527,151 @@ __global__ void __launch_bounds__(PME_BLOCK) k_pme_solve32(const SegDev* __restr
 // KIND 0: forces from phi (pphi, or pgr for displaced configurations); KIND 1: H v
 // from pphi and the dipole potential in pgr (FP32).  outsel 0, 1, 2: added to the float4 pair
 // output f32, hv32, f32m; outsel 3, 4: written to the FP64 buffer frec, hrec.
+// One workgroup per (bead, tile), which holds the tile's potentials in LDS with the P - 1
+// points below it that its atoms reach: each atom reads 64 values (P = 4) per potential at
+// addresses that differ from lane to lane, which from the L1 cost a pass per line and
+// bounded the kernel.  150000 sites x 16 beads: forces 206 -> 120 us, H v 459 -> 181 us, the
+// gradient call 10.3 -> 9.8 ms; 3000 sites x 16 beads, where filling the tile takes longest:
+// 8.4 -> 10.9 and 12.9 -> 14.8 us beside the pair kernels, which end later (call unchanged).
+constexpr int GATHER_BLOCK = 128;
+
 template <int P, int KIND>
-__global__ void __launch_bounds__(EWB) k_pme_gather(const SegDev* __restrict__ segs, int nb,
-                                                    char* ws, const double* __restrict__ R,
-                                                    const double* __restrict__ V, int fdsign,
-                                                    double fdh, int outsel, int use_pgr) {
+__global__ void __launch_bounds__(GATHER_BLOCK) k_pme_gather(const SegDev* __restrict__ segs, int nb,
+                                                             char* ws, const double* __restrict__ V,
+                                                             int outsel, int use_pgr) {
+    extern __shared__ double s_phi[];
     const SegDev& sg = segs[0];
     const SysDev& s = sg.s;
-    const int b = blockIdx.x / sg.bpb;
-    const int slot = (blockIdx.x - b * sg.bpb) * EWB + threadIdx.x;
-    if (b >= nb || slot >= s.Q) return;
-    // atoms in tile order: the lanes of a wave read neighbouring grid points
-    const int4 ab = wsp<const int4>(ws, sg.o_ptb)[(size_t)b * s.Q + slot];
-    const double4 aw = wsp<const double4>(ws, sg.o_ptw)[(size_t)b * s.Q + slot];
-    const int i = ab.w;
-    int ix[P], iy[P], iz[P];
-    support<P>(ab.x, s.Kg[0], ix);
-    support<P>(ab.y, s.Kg[1], iy);
-    support<P>(ab.z, s.Kg[2], iz);
-    double tx[P], ty[P], tz[P], dx[P], dy[P], dz[P], hx[P], hy[P], hz[P];
-    constexpr int DER = KIND == 0 ? 1 : 2;
-    bspline<P, DER>(aw.x, tx, dx, hx);
-    bspline<P, DER>(aw.y, ty, dy, hy);
-    bspline<P, DER>(aw.z, tz, dz, hz);
-    const size_t Kt = (size_t)s.Kg[0] * s.Kg[1] * s.Kg[2];
-    const double* phi = wsp<const double>(ws, (KIND == 0 && use_pgr) ? sg.o_pgr : sg.o_pphi) +
-                        (size_t)b * Kt;
-    const float* dphi = wsp<const float>(ws, sg.o_pgr) + (size_t)b * Kt;
-    double vx = 0.0, vy = 0.0, vz = 0.0;
-    if (KIND == 1) {
-        const double* v = V + ((size_t)b * s.Q + i) * 3;
-        vx = v[0] * s.kl[0];
-        vy = v[1] * s.kl[1];
-        vz = v[2] * s.kl[2];
+    const int b = blockIdx.x / s.ntile;
+    const int t = blockIdx.x - b * s.ntile;
+    if (b >= nb) return;
+    const int* start = wsp<const int>(ws, sg.o_pts) + (size_t)b * (s.ntile + 1) + t;
+    const int a0 = start[0], a1 = start[1];
+    if (a0 == a1) return;
+    const int t2 = t % s.ntl[2], t1 = (t / s.ntl[2]) % s.ntl[1], t0 = t / (s.ntl[2] * s.ntl[1]);
+    const int tt[3] = {t0, t1, t2};
+    int lo[3], n[3];  // first point held (tile minus P - 1) and points held per axis
+    for (int a = 0; a < 3; ++a) {
+        const int* e = s.tile_lo + s.tlo_off[a] + tt[a];
+        lo[a] = e[0] - (P - 1);
+        n[a] = e[1] - lo[a];
     }
-    // Sums over z first (per x-y pair of spline points), 32-bit grid indices:
-    //   St = sum_f phi tz, Sd = sum_f phi dz, Sh = sum_f phi hz, Tt / Td the same of dphi.
-    // Force:  a = sum_{a,e} (dx ty St, tx dy St, tx ty Sd)
-    // H v:    a = sum_{a,e} grad(theta) . dphi + (grad grad theta) v phi, expanded by axis.
-    double ax = 0.0, ay = 0.0, az = 0.0;
-    const int K1 = s.Kg[1], K2 = s.Kg[2];
+    const size_t Kt = (size_t)s.Kg[0] * s.Kg[1] * s.Kg[2];
+    const double* phi = wsp<const double>(ws, (KIND == 0 && use_pgr) ? sg.o_pgr : sg.o_pphi) + (size_t)b * Kt;
+    const float* dphi = wsp<const float>(ws, sg.o_pgr) + (size_t)b * Kt;
+    const int nn = n[0] * n[1] * n[2];
+    float* s_dphi = reinterpret_cast<float*>(s_phi + nn);
+    // k / n for k < 22^3 and 4 <= n <= 22 as a product: the excess k n / 2^20 stays below 1
+    const unsigned r2 = ((1u << 20) + n[2] - 1) / n[2], r1 = ((1u << 20) + n[1] - 1) / n[1];
+    constexpr int AHEAD = 6;  // loads of a thread in flight (one at a time: 13.1, not 10.9 us at 3000 x 16)
+    for (int k0 = threadIdx.x; k0 < nn; k0 += AHEAD * GATHER_BLOCK) {
+        double p[AHEAD];
+        float q[AHEAD];
 #pragma unroll
-    for (int a = 0; a < P; ++a) {
+        for (int u = 0; u < AHEAD; ++u) {
+            const unsigned k = min(k0 + u * GATHER_BLOCK, nn - 1);
+            const unsigned r = (k * r2) >> 20, x = (r * r1) >> 20;
+            int g[3] = {(int)x + lo[0], (int)(r - x * n[1]) + lo[1], (int)(k - r * n[2]) + lo[2]};
+            // at least P points per axis and P - 1 below: one period suffices
+            for (int a = 0; a < 3; ++a) g[a] += g[a] < 0 ? s.Kg[a] : 0;
+            const int o = (g[0] * s.Kg[1] + g[1]) * s.Kg[2] + g[2];
+            p[u] = phi[o];
+            if (KIND == 1) q[u] = dphi[o];
+        }
 #pragma unroll
-        for (int e = 0; e < P; ++e) {
-            const int row = (ix[a] * K1 + iy[e]) * K2;
-            const double txy = tx[a] * ty[e], dxy = dx[a] * ty[e], xdy = tx[a] * dy[e];
-            double St = 0.0, Sd = 0.0, Sh = 0.0, Tt = 0.0, Td = 0.0;
-#pragma unroll
-            for (int f = 0; f < P; ++f) {
-                const double p = phi[row + iz[f]];
-                St = fma(p, tz[f], St);
-                Sd = fma(p, dz[f], Sd);
-                if (KIND == 1) {
-                    const double q = (double)dphi[row + iz[f]];
-                    Sh = fma(p, hz[f], Sh);
-                    Tt = fma(q, tz[f], Tt);
-                    Td = fma(q, dz[f], Td);
-                }
-            }
-            if (KIND == 0) {
-                ax = fma(dxy, St, ax);
-                ay = fma(xdy, St, ay);
-                az = fma(txy, Sd, az);
-            } else {
-                const double hxx = hx[a] * ty[e], hyy = tx[a] * hy[e], hxy = dx[a] * dy[e];
-                ax = fma(dxy, Tt, fma(fma(hxx, vx, hxy * vy), St, fma(dxy * vz, Sd, ax)));
-                ay = fma(xdy, Tt, fma(fma(hxy, vx, hyy * vy), St, fma(xdy * vz, Sd, ay)));
-                az = fma(txy, Td, fma(fma(dxy, vx, xdy * vy), Sd, fma(txy * vz, Sh, az)));
+        for (int u = 0; u < AHEAD; ++u) {
+            const int k = k0 + u * GATHER_BLOCK;
+            if (k < nn) {
+                s_phi[k] = p[u];
+                if (KIND == 1) s_dphi[k] = q[u];
             }
         }
     }
-    (void)hx;
-    (void)hy;
-    (void)hz;
-    const double qi = aw.w;
-    double o[3];
-    if (KIND == 0) {
-        o[0] = -qi * s.kl[0] * ax;
-        o[1] = -qi * s.kl[1] * ay;
-        o[2] = -qi * s.kl[2] * az;
-    } else {
-        o[0] = qi * s.kl[0] * ax;
-        o[1] = qi * s.kl[1] * ay;
-        o[2] = qi * s.kl[2] * az;
+    __syncthreads();
+    for (int slot = a0 + (int)threadIdx.x; slot < a1; slot += GATHER_BLOCK) {
+        const int4 ab = wsp<const int4>(ws, sg.o_ptb)[(size_t)b * s.Q + slot];
+        const double4 aw = wsp<const double4>(ws, sg.o_ptw)[(size_t)b * s.Q + slot];
+        const int i = ab.w;
+        double tx[P], ty[P], tz[P], dx[P], dy[P], dz[P], hx[P], hy[P], hz[P];
+        constexpr int DER = KIND == 0 ? 1 : 2;
+        bspline<P, DER>(aw.x, tx, dx, hx);
+        bspline<P, DER>(aw.y, ty, dy, hy);
+        bspline<P, DER>(aw.z, tz, dz, hz);
+        double vx = 0.0, vy = 0.0, vz = 0.0;
+        if (KIND == 1) {
+            const double* v = V + ((size_t)b * s.Q + i) * 3;
+            vx = v[0] * s.kl[0];
+            vy = v[1] * s.kl[1];
+            vz = v[2] * s.kl[2];
+        }
+        // Sums over z first (per x-y pair of spline points):
+        //   St = sum_f phi tz, Sd = sum_f phi dz, Sh = sum_f phi hz, Tt / Td the same of dphi.
+        // Force:  a = sum_{a,e} (dx ty St, tx dy St, tx ty Sd)
+        // H v:    a = sum_{a,e} grad(theta) . dphi + (grad grad theta) v phi, expanded by axis.
+        double ax = 0.0, ay = 0.0, az = 0.0;
+        const int base = ((ab.x - lo[0]) * n[1] + (ab.y - lo[1])) * n[2] + (ab.z - lo[2]);
+#pragma unroll
+        for (int a = 0; a < P; ++a) {
+#pragma unroll
+            for (int e = 0; e < P; ++e) {
+                const int row = base - (a * n[1] + e) * n[2];
+                const double txy = tx[a] * ty[e], dxy = dx[a] * ty[e], xdy = tx[a] * dy[e];
+                double St = 0.0, Sd = 0.0, Sh = 0.0, Tt = 0.0, Td = 0.0;
+#pragma unroll
+                for (int f = 0; f < P; ++f) {
+                    const double p = s_phi[row - f];
+                    St = fma(p, tz[f], St);
+                    Sd = fma(p, dz[f], Sd);
+                    if (KIND == 1) {
+                        const double q = (double)s_dphi[row - f];
+                        Sh = fma(p, hz[f], Sh);
+                        Tt = fma(q, tz[f], Tt);
+                        Td = fma(q, dz[f], Td);
+                    }
+                }
+                if (KIND == 0) {
+                    ax = fma(dxy, St, ax);
+                    ay = fma(xdy, St, ay);
+                    az = fma(txy, Sd, az);
+                } else {
+                    const double hxx = hx[a] * ty[e], hyy = tx[a] * hy[e], hxy = dx[a] * dy[e];
+                    ax = fma(dxy, Tt, fma(fma(hxx, vx, hxy * vy), St, fma(dxy * vz, Sd, ax)));
+                    ay = fma(xdy, Tt, fma(fma(hxy, vx, hyy * vy), St, fma(xdy * vz, Sd, ay)));
+                    az = fma(txy, Td, fma(fma(dxy, vx, xdy * vy), Sd, fma(txy * vz, Sh, az)));
+                }
+            }
+        }
+        (void)hx;
+        (void)hy;
+        (void)hz;
+        const double qi = aw.w;
+        double o[3];
+        if (KIND == 0) {
+            o[0] = -qi * s.kl[0] * ax;
+            o[1] = -qi * s.kl[1] * ay;
+            o[2] = -qi * s.kl[2] * az;
+        } else {
+            o[0] = qi * s.kl[0] * ax;
+            o[1] = qi * s.kl[1] * ay;
+            o[2] = qi * s.kl[2] * az;
+        }
+        if (outsel >= 3) {
+            double* d = wsp<double>(ws, outsel == 3 ? sg.o_frec : sg.o_hrec) + ((size_t)b * s.Q + i) * 3;
+            d[0] = o[0];
+            d[1] = o[1];
+            d[2] = o[2];
+            continue;
+        }
+        size_t off = sg.o_f32;
+        if (outsel == 1) off = sg.o_hv32;
+        else if (outsel == 2) off = sg.o_f32m;
+        float4* out = wsp<float4>(ws, off) + (size_t)b * s.Q + i;
+        float4 t4 = *out;
+        t4.x = (float)((double)t4.x + o[0]);
+        t4.y = (float)((double)t4.y + o[1]);
+        t4.z = (float)((double)t4.z + o[2]);
+        *out = t4;
     }
-    if (outsel >= 3) {
-        double* d = wsp<double>(ws, outsel == 3 ? sg.o_frec : sg.o_hrec) + ((size_t)b * s.Q + i) * 3;
-        d[0] = o[0];
-        d[1] = o[1];
-        d[2] = o[2];
-        return;
-    }
-    size_t off = sg.o_f32;
-    if (outsel == 1) off = sg.o_hv32;
-    else if (outsel == 2) off = sg.o_f32m;
-    float4* out = wsp<float4>(ws, off) + (size_t)b * s.Q + i;
-    float4 t = *out;
-    t.x = (float)((double)t.x + o[0]);
-    t.y = (float)((double)t.y + o[1]);
-    t.z = (float)((double)t.z + o[2]);
-    *out = t;
 }
 
 // Largest |v_i|^2 per bead into the per-bead max (zeroed by the binning), for the
@@ -669,16 +713,17 @@ void spread_p(const SegDev* dsegs, const SegDev& h, int nb, int nbatch, char* ws
 }
 
 template <int P>
-void gather_p(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* R,
-              const double* V, int kind, int fdsign, double fdh, int outsel, int use_pgr,
-              hipStream_t st) {
-    const dim3 grid(nb * h.bpb);
+void gather_p(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* V, int kind,
+              int outsel, int use_pgr, hipStream_t st) {
+    const dim3 grid(nb * h.s.ntile);
+    size_t pts = 1;
+    for (int a = 0; a < 3; ++a) pts *= (size_t)h.s.tile_max[a] + P - 1;
     if (kind == 0)
-        hipLaunchKernelGGL((k_pme_gather<P, 0>), grid, dim3(EWB), 0, st, dsegs, nb, ws, R, V, fdsign,
-                           fdh, outsel, use_pgr);
+        hipLaunchKernelGGL((k_pme_gather<P, 0>), grid, dim3(GATHER_BLOCK), pts * 8, st, dsegs, nb, ws, V,
+                           outsel, use_pgr);
     else
-        hipLaunchKernelGGL((k_pme_gather<P, 1>), grid, dim3(EWB), 0, st, dsegs, nb, ws, R, V, fdsign,
-                           fdh, outsel, use_pgr);
+        hipLaunchKernelGGL((k_pme_gather<P, 1>), grid, dim3(GATHER_BLOCK), pts * 12, st, dsegs, nb, ws, V,
+                           outsel, use_pgr);
 }
 
 }  // namespace
@@ -720,13 +765,12 @@ void run_pme_solve32(const SegDev* dsegs, const SegDev& h, int nb, char* ws, hip
     hipLaunchKernelGGL(k_pme_solve32, dim3(nb * h.s.nsb), dim3(PME_BLOCK), 0, st, dsegs, nb, ws);
 }
 
-void run_pme_gather(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* R,
-                    const double* V, int kind, int fdsign, double fdh, int outsel, int use_pgr,
-                    hipStream_t st) {
+void run_pme_gather(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* V,
+                    int kind, int outsel, int use_pgr, hipStream_t st) {
     switch (h.s.pme_p) {
-        case 6: gather_p<6>(dsegs, h, nb, ws, R, V, kind, fdsign, fdh, outsel, use_pgr, st); break;
-        case 8: gather_p<8>(dsegs, h, nb, ws, R, V, kind, fdsign, fdh, outsel, use_pgr, st); break;
-        default: gather_p<4>(dsegs, h, nb, ws, R, V, kind, fdsign, fdh, outsel, use_pgr, st); break;
+        case 6: gather_p<6>(dsegs, h, nb, ws, V, kind, outsel, use_pgr, st); break;
+        case 8: gather_p<8>(dsegs, h, nb, ws, V, kind, outsel, use_pgr, st); break;
+        default: gather_p<4>(dsegs, h, nb, ws, V, kind, outsel, use_pgr, st); break;
     }
 }
 

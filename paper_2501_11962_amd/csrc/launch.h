@@ -76,9 +76,8 @@ void run_pme_solve(const SegDev* dsegs, const SegDev& h, int nb, char* ws, int w
 void run_pme_solve32(const SegDev* dsegs, const SegDev& h, int nb, char* ws, hipStream_t st);
 // outsel: added to 0 f32, 1 hv32, 2 f32m (float4); written to 3 frec, 4 hrec (FP64);
 // use_pgr: kind-0 potential read from pgr instead of pphi.
-void run_pme_gather(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* R,
-                    const double* V, int kind, int fdsign, double fdh, int outsel, int use_pgr,
-                    hipStream_t st);
+void run_pme_gather(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* V, int kind,
+                    int outsel, int use_pgr, hipStream_t st);
 void run_pme_vmax(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* V,
                   hipStream_t st);
 

@@ -580,6 +580,7 @@ int mop_system_create(mop_ctx ctx, const mop_system_desc* d, mop_system* out) {
         }
         s.ntile = s.ntl[0] * s.ntl[1] * s.ntl[2];
         s.tile_pts = maxe[0] * maxe[1] * maxe[2];
+        for (int a = 0; a < 3; ++a) s.tile_max[a] = maxe[a];
     }
     // per atom
     std::vector<float> qs(Q);
@@ -882,8 +883,7 @@ static void pme_forces(const mop_plan_s* pl, int nb, const CallPtrs& cp, int fds
     run_pme_solve(pl->dseg, h, nb, ws, fdsign == 0 ? 1 : 0, st);
     run_fft(pl, false, ws + h.o_pgc, ws + (fdsign == 0 ? h.o_pphi : h.o_pgr), ws + h.o_pfw, st);
     if (gather)
-        run_pme_gather(pl->dseg, h, nb, ws, cp.R, nullptr, 0, fdsign, cp.fd_h, outsel,
-                       fdsign != 0 ? 1 : 0, st);
+        run_pme_gather(pl->dseg, h, nb, ws, nullptr, 0, outsel, fdsign != 0 ? 1 : 0, st);
 }
 
 // PME reciprocal H v of nb pair beads (V: [nb][Q][3]; needs pphi and the tile order of
@@ -896,7 +896,7 @@ static void pme_hvp(const mop_plan_s* pl, int nb, const CallPtrs& cp, const doub
     run_fft(pl, true, ws + h.o_pgr, ws + h.o_pgc, ws + h.o_pfw, st, true);
     run_pme_solve32(pl->dseg, h, nb, ws, st);
     run_fft(pl, false, ws + h.o_pgc, ws + h.o_pgr, ws + h.o_pfw, st, true);
-    run_pme_gather(pl->dseg, h, nb, ws, cp.R, V, 1, 0, 0.0, 4, 0, st);
+    run_pme_gather(pl->dseg, h, nb, ws, V, 1, 4, 0, st);
 }
 
 // Fork: work enqueued on the plan's side stream after this waits for everything enqueued

@@ -123,8 +123,9 @@ struct SysDev {
     const double* phihat; // [Kx Ky Kzh] f B(m) C(m), half spectrum
     // grid tiles of the spreading kernel: ntl[a] tiles per axis with edges
     // tile_lo[tlo_off[a] + t] (balanced, each at least PME_TILE points unless the axis is
-    // shorter), tile_of[tof_off[a] + k] the tile of grid index k; tile_pts = largest tile
-    int ntl[3], ntile, tile_pts;
+    // shorter), tile_of[tof_off[a] + k] the tile of grid index k; tile_pts = largest tile,
+    // tile_max its edges
+    int ntl[3], ntile, tile_pts, tile_max[3];
     int tlo_off[3], tof_off[3];
     const int* tile_lo;
     const int* tile_of;
