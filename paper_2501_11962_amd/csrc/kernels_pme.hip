@@ -410,51 +410,64 @@ __global__ void __launch_bounds__(PME_BLOCK) k_pme_spread(const SegDev* __restri
         if (threadIdx.x == 0) ncand = 0;
         __syncthreads();
         const int lane = threadIdx.x & 63;
+        // The atoms of the tile and of its upper neighbours, as one sequence (a loop per tile
+        // left half of the threads idle and waited for the tile starts eight times: 21 -> 18.5 us
+        // at 3000 sites x 16 beads, charges 479 -> 415 us at 150000 x 16).
         const int nx = s.ntl[0] > 1 ? 2 : 1, ny = s.ntl[1] > 1 ? 2 : 1, nz = s.ntl[2] > 1 ? 2 : 1;
-        for (int n = 0; n < nx * ny * nz; ++n) {
-            const int ux = (tx + n / (ny * nz)) % s.ntl[0];
-            const int uy = (ty + (n / nz) % ny) % s.ntl[1];
-            const int uz = (tz + n % nz) % s.ntl[2];
-            const int u = (ux * s.ntl[1] + uy) * s.ntl[2] + uz;
-            for (int k0 = start[u]; k0 < start[u + 1]; k0 += PME_BLOCK) {
-                // keep the atoms whose spline support meets this tile (list them in LDS)
-                const int k = k0 + threadIdx.x;
-                unsigned m = 0;
-                if (k < start[u + 1]) {
-                    const int4 ab = pb[k];
-                    int ix[P], iy[P], iz[P];
-                    support<P>(ab.x, s.Kg[0], ix);
-                    support<P>(ab.y, s.Kg[1], iy);
-                    support<P>(ab.z, s.Kg[2], iz);
-                    unsigned mx = 0, my = 0, mz = 0;
+        int first[8], past[8];  // a tile's first atom; atoms of the sequence up to its end
 #pragma unroll
-                    for (int j = 0; j < P; ++j) {
-                        mx |= (unsigned)(ix[j] >= lo[0] && ix[j] < lo[0] + ex) << j;
-                        my |= (unsigned)(iy[j] >= lo[1] && iy[j] < lo[1] + ey) << j;
-                        mz |= (unsigned)(iz[j] >= lo[2] && iz[j] < lo[2] + ez) << j;
-                    }
-                    if (mx && my && mz) m = mx | (my << 8) | (mz << 16);
+        for (int n = 0; n < 8; ++n) {
+            const int ix = n >> 2, iy = (n >> 1) & 1, iz = n & 1;
+            int u = -1;
+            if (ix < nx && iy < ny && iz < nz)
+                u = (((tx + ix) % s.ntl[0]) * s.ntl[1] + (ty + iy) % s.ntl[1]) * s.ntl[2] + (tz + iz) % s.ntl[2];
+            first[n] = u >= 0 ? start[u] : 0;
+            past[n] = u >= 0 ? start[u + 1] - first[n] : 0;
+        }
+#pragma unroll
+        for (int n = 1; n < 8; ++n) past[n] += past[n - 1];
+        for (int k0 = 0; k0 < past[7]; k0 += PME_BLOCK) {
+            // keep the atoms whose spline support meets this tile (list them in LDS)
+            const int q = k0 + threadIdx.x;
+            int k = first[0] + q;
+#pragma unroll
+            for (int n = 1; n < 8; ++n)
+                if (q >= past[n - 1]) k = first[n] + q - past[n - 1];
+            unsigned m = 0;
+            if (q < past[7]) {
+                const int4 ab = pb[k];
+                int ix[P], iy[P], iz[P];
+                support<P>(ab.x, s.Kg[0], ix);
+                support<P>(ab.y, s.Kg[1], iy);
+                support<P>(ab.z, s.Kg[2], iz);
+                unsigned mx = 0, my = 0, mz = 0;
+#pragma unroll
+                for (int j = 0; j < P; ++j) {
+                    mx |= (unsigned)(ix[j] >= lo[0] && ix[j] < lo[0] + ex) << j;
+                    my |= (unsigned)(iy[j] >= lo[1] && iy[j] < lo[1] + ey) << j;
+                    mz |= (unsigned)(iz[j] >= lo[2] && iz[j] < lo[2] + ez) << j;
                 }
-                const unsigned long long bal = __ballot(m != 0);
-                int base = 0;
-                if (lane == 0 && bal) base = atomicAdd(&ncand, (int)__popcll(bal));
-                base = __shfl(base, 0, 64);
-                if (m) {
-                    const int pos = base + (int)__builtin_amdgcn_mbcnt_hi(
-                                               (unsigned)(bal >> 32),
-                                               __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-                    cand_k[pos] = k;
-                    cand_m[pos] = (int)m;
-                }
+                if (mx && my && mz) m = mx | (my << 8) | (mz << 16);
+            }
+            const unsigned long long bal = __ballot(m != 0);
+            int base = 0;
+            if (lane == 0 && bal) base = atomicAdd(&ncand, (int)__popcll(bal));
+            base = __shfl(base, 0, 64);
+            if (m) {
+                const int pos = base + (int)__builtin_amdgcn_mbcnt_hi(
+                                           (unsigned)(bal >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+                cand_k[pos] = k;
+                cand_m[pos] = (int)m;
+            }
+            __syncthreads();
+            const int nc = ncand;
+            __syncthreads();  // every thread has read the count before it changes again
+            if (nc > SPREAD_CAP - PME_BLOCK) {  // room for one more round of appends
+                flush(nc);
                 __syncthreads();
-                const int nc = ncand;
-                __syncthreads();  // every thread has read the count before it changes again
-                if (nc > SPREAD_CAP - PME_BLOCK) {  // room for one more round of appends
-                    flush(nc);
-                    __syncthreads();
-                    if (threadIdx.x == 0) ncand = 0;
-                    __syncthreads();
-                }
+                if (threadIdx.x == 0) ncand = 0;
+                __syncthreads();
             }
         }
         flush(ncand);
