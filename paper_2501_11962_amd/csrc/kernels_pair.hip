@@ -20,10 +20,12 @@
 //   The force pass records each cluster's neighbour list (one record per candidate
 //   cluster with survivors); the Hessian pass of the same bead replays it instead of
 //   steps 1-2: the records' atom masks give the slot list directly.
-//   What bounds the kernels is the issue time of vector instructions (LDS and memory have
-//   slack), and on gfx950 their rates differ: FP32 add, multiply and fma, 32-bit integer
-//   add and bitwise operations on vector registers take 2 cycles per wave and SIMD; the
-//   same with a scalar-register operand, and compares, conversions, shifts, min / max,
+//   What bounds the kernels is the issue time of vector instructions, with LDS (active 62%
+//   of the time in the force kernel, 52% in the Hessian) and instruction fetch (0.38 per CU
+//   and cycle; two CUs share a cache) not far behind, at clocks that the power limit sets
+//   (1.75 to 2.2 GHz).  On gfx950 instruction rates differ: FP32 add, multiply and fma, 32-bit
+//   integer add and bitwise operations on vector registers take 2 cycles per wave and SIMD;
+//   the same with a scalar-register operand, and compares, conversions, shifts, min / max,
 //   three-operand integer operations, DPP forms and v_mbcnt 4; rsq, rcp and exp 8 (timed
 //   in loops of independent instructions, 8 waves per SIMD).  Only survivors are therefore
 //   converted, charged and written to the ring, all 64 lanes at work: of the candidates
@@ -172,7 +174,7 @@ constexpr bool THREE_Q = MODE == 1 && N3 == 0 && EL == 0;
 // the kernels agree bit for bit.
 // toff: byte offset of type j in the table row (XSKIP kernels; the others take the type
 // from kj); EXCL: the pair may be excluded (kj is read).
-// round3: r^-3 is rounded before it is taken from 2 k_rf (force, reaction field).
+// cube_first: r^-3 is rounded before it is taken from 2 k_rf (force, reaction field).
 template <int MODE, bool EX, bool WANTE, bool T_OUT, int EL, bool Q3, bool EXCL>
 __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const float4* tabrow,
                                           int ntab,
@@ -180,7 +182,7 @@ __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const 
                                           float qj, uint32_t toff, uint32_t kj, float vjx, float vjy,
                                           float vjz, bool valid, float& ax, float& ay,
                                           float& az, float& tx, float& ty, float& tz,
-                                          float& en, bool round3 = false) {
+                                          float& en, bool cube_first = false) {
 #pragma clang fp contract(off)
     float dx, dy, dz;
     if (EX) {
@@ -218,7 +220,7 @@ __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const 
         if (EL == 0) {
             g = G6 * rinv8;
             g = fmaf(qq, Q3 ? fmaf(rinv3, -1.0f / 3.0f, P.krf2_3)
-                            : (round3 ? P.krf2 - rinv3 : fmaf(-rinv, rinv2, P.krf2)), g);
+                            : (cube_first ? P.krf2 - rinv3 : fmaf(-rinv, rinv2, P.krf2)), g);
             g = fmaf(C1, rinv, g);
         } else {
             r = r2 * rinv;
@@ -1004,9 +1006,11 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
 
 // Waves per SIMD the pair kernels are compiled for (register budget 512 / waves, in
 // steps of 8): 6 (80 registers) for the reaction-field force kernel without energies and
-// the full-shell reaction-field Hessian kernel, 5 (96) for the rest; every flat-grid
-// kernel fits without spills.  Measured per veff_grad call on the 150,000-atom workload
-// against 4 waves (128 registers): -7.5% with reaction field, -1.5% with particle-mesh
+// the full-shell reaction-field Hessian kernel, 4 (128) for the Newton-3 force kernel with
+// energies, 5 (96) for the rest.  A few set-up values spill (16 to 36 bytes per lane in the
+// flat kernels, none of them read per step; 5 waves without spills: +5%).  Measured per
+// veff_grad call on the 150,000-atom workload against 4 waves (128
+// registers): -7.5% with reaction field, -1.5% with particle-mesh
 // Ewald (whose mesh kernels on the second stream need room beside the pair kernels).  The
 // wave index is made scalar (readfirstlane) and the lane exchanges use swizzles
 // (lane_xor), so that per-wave pointers and shuffle bounds take no vector registers.
