@@ -138,7 +138,8 @@ __device__ __forceinline__ void bin_range(const SegDev& sg, char* ws, int b, int
 
 // Reserve places: the atoms of each bin in the order of their atomic ranks.
 __global__ void __launch_bounds__(EWB) k_bin_scatter(const SegDev* __restrict__ segs, Launch L, char* ws) {
-    const int blk = blockIdx.x;
+    const int blk = xcd_block(L.pf[L.nseg]);
+    if (blk < 0) return;
     const int p = find_seg(L, blk);
     const SegDev& sg = segs[p];
     const int local = blk - L.pf[p];
@@ -155,7 +156,8 @@ __global__ void __launch_bounds__(EWB) k_bin_scatter(const SegDev* __restrict__ 
 // Place each atom at its bin's first slot plus the number of atoms of the bin with a
 // smaller index.
 __global__ void __launch_bounds__(EWB) k_bin_place(const SegDev* __restrict__ segs, Launch L, char* ws) {
-    const int blk = blockIdx.x;
+    const int blk = xcd_block(L.pf[L.nseg]);
+    if (blk < 0) return;
     const int p = find_seg(L, blk);
     const SegDev& sg = segs[p];
     const int local = blk - L.pf[p];
@@ -284,7 +286,8 @@ __device__ __forceinline__ bool overlaps(const SysDev& s, int si, uint32_t ux, u
 }
 
 __global__ void __launch_bounds__(EWB) k_overlap(const SegDev* __restrict__ segs, Launch L, char* ws) {
-    const int blk = blockIdx.x;
+    const int blk = xcd_block(L.pf[L.nseg]);
+    if (blk < 0) return;
     const int p = find_seg(L, blk);
     const SegDev& sg = segs[p];
     const int local = blk - L.pf[p];
@@ -606,7 +609,7 @@ static void launch_overlap(const SegDev* dsegs, const SegDev* hsegs, const Launc
     for (int p = 0; p < base.nseg; ++p)
         L.pf[p + 1] = L.pf[p] + base.nb[p] * ((hsegs[p].s.S + EWB - 1) / EWB);
     if (L.pf[base.nseg] > 0)
-        hipLaunchKernelGGL(k_overlap, dim3(L.pf[base.nseg]), dim3(EWB), 0, st, dsegs, L, ws);
+        hipLaunchKernelGGL(k_overlap, dim3(xcd_grid(L.pf[base.nseg])), dim3(EWB), 0, st, dsegs, L, ws);
 }
 
 void run_binning(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char* ws,
@@ -669,8 +672,8 @@ static void bin_general(const SegDev* dsegs, const SegDev* hsegs, const Launch& 
     Lb.pf[0] = 0;
     for (int p = 0; p < base.nseg; ++p) Lb.pf[p + 1] = Lb.pf[p] + base.nb[p];
     hipLaunchKernelGGL(k_bin_colstart, dim3(Lb.pf[base.nseg]), dim3(CSB), 0, st, dsegs, Lb, ws);
-    hipLaunchKernelGGL(k_bin_scatter, dim3(La.pf[base.nseg]), dim3(EWB), 0, st, dsegs, La, ws);
-    hipLaunchKernelGGL(k_bin_place, dim3(La.pf[base.nseg]), dim3(EWB), 0, st, dsegs, La, ws);
+    hipLaunchKernelGGL(k_bin_scatter, dim3(xcd_grid(La.pf[base.nseg])), dim3(EWB), 0, st, dsegs, La, ws);
+    hipLaunchKernelGGL(k_bin_place, dim3(xcd_grid(La.pf[base.nseg])), dim3(EWB), 0, st, dsegs, La, ws);
     hipLaunchKernelGGL(k_bin_pad, dim3(Lc.pf[base.nseg]), dim3(EWB), 0, st, dsegs, Lc, ws);
 }
 

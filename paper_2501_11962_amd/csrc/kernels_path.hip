@@ -36,7 +36,8 @@ __device__ __forceinline__ void add_mesh(const SegDev& sg, char* ws, size_t off,
 __global__ void __launch_bounds__(EWB) k_resid(const SegDev* __restrict__ segs, Launch L,
                                                CallPtrs cp, int want_dmax) {
     __shared__ double sh[3][EWB / 64];
-    const int blk = blockIdx.x;
+    const int blk = xcd_block(L.pf[L.nseg]);
+    if (blk < 0) return;
     const int p = find_seg(L, blk);
     const SegDev& sg = segs[p];
     const SysDev& s = sg.s;
@@ -330,7 +331,7 @@ static Launch per_bead_blocks(const Launch& base, const SegDev* hsegs, bool resi
 void run_resid(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, const CallPtrs& cp,
                int want_dmax, hipStream_t st) {
     const Launch L = per_bead_blocks(base, hsegs, true, false);
-    hipLaunchKernelGGL(k_resid, dim3(L.pf[L.nseg]), dim3(EWB), 0, st, dsegs, L, cp, want_dmax);
+    hipLaunchKernelGGL(k_resid, dim3(xcd_grid(L.pf[L.nseg])), dim3(EWB), 0, st, dsegs, L, cp, want_dmax);
 }
 
 void run_assemble(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, const CallPtrs& cp,

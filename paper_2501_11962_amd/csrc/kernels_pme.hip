@@ -167,8 +167,10 @@ __global__ void __launch_bounds__(EWB) k_pme_tile_count(const SegDev* __restrict
                                                         int fdsign, double fdh) {
     const SegDev& sg = segs[0];
     const SysDev& s = sg.s;
-    const int b = blockIdx.x / sg.bpb;
-    const int i = (blockIdx.x - b * sg.bpb) * EWB + threadIdx.x;
+    const int blk = xcd_block(nb * sg.bpb);
+    if (blk < 0) return;
+    const int b = blk / sg.bpb;
+    const int i = (blk - b * sg.bpb) * EWB + threadIdx.x;
     if (b >= nb) return;
     const bool valid = i < s.Q;
     int tile = -1;
@@ -246,8 +248,10 @@ __global__ void __launch_bounds__(EWB) k_pme_tile_scatter(const SegDev* __restri
                                                           int fdsign, double fdh) {
     const SegDev& sg = segs[0];
     const SysDev& s = sg.s;
-    const int b = blockIdx.x / sg.bpb;
-    const int i = (blockIdx.x - b * sg.bpb) * EWB + threadIdx.x;
+    const int blk = xcd_block(nb * sg.bpb);
+    if (blk < 0) return;
+    const int b = blk / sg.bpb;
+    const int i = (blk - b * sg.bpb) * EWB + threadIdx.x;
     if (b >= nb || i >= s.Q) return;
     const size_t o = (size_t)b * s.Q + i;
     const int tile = wsp<const int>(ws, sg.o_ptid)[o];
@@ -555,8 +559,10 @@ __global__ void __launch_bounds__(GATHER_BLOCK) k_pme_gather(const SegDev* __res
     extern __shared__ double s_phi[];
     const SegDev& sg = segs[0];
     const SysDev& s = sg.s;
-    const int b = blockIdx.x / s.ntile;
-    const int t = blockIdx.x - b * s.ntile;
+    const int blk = xcd_block(nb * s.ntile);
+    if (blk < 0) return;
+    const int b = blk / s.ntile;
+    const int t = blk - b * s.ntile;
     if (b >= nb) return;
     const int* start = wsp<const int>(ws, sg.o_pts) + (size_t)b * (s.ntile + 1) + t;
     const int a0 = start[0], a1 = start[1];
@@ -728,7 +734,7 @@ void spread_p(const SegDev* dsegs, const SegDev& h, int nb, int nbatch, char* ws
 template <int P>
 void gather_p(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* V, int kind,
               int outsel, int use_pgr, hipStream_t st) {
-    const dim3 grid(nb * h.s.ntile);
+    const dim3 grid(xcd_grid(nb * h.s.ntile));
     size_t pts = 1;
     for (int a = 0; a < 3; ++a) pts *= (size_t)h.s.tile_max[a] + P - 1;
     if (kind == 0)
@@ -752,10 +758,10 @@ void run_pme_sort(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const 
     const int n = nb * h.s.ntile;
     hipLaunchKernelGGL(k_pme_tile_zero, dim3((n + PME_BLOCK - 1) / PME_BLOCK), dim3(PME_BLOCK), 0, st,
                        dsegs, n, ws);
-    hipLaunchKernelGGL(k_pme_tile_count, dim3(nb * h.bpb), dim3(EWB), 0, st, dsegs, nb, ws, R, fdsign,
+    hipLaunchKernelGGL(k_pme_tile_count, dim3(xcd_grid(nb * h.bpb)), dim3(EWB), 0, st, dsegs, nb, ws, R, fdsign,
                        fdh);
     hipLaunchKernelGGL(k_pme_tile_scan, dim3(nb), dim3(SCAN_BLOCK), 0, st, dsegs, ws);
-    hipLaunchKernelGGL(k_pme_tile_scatter, dim3(nb * h.bpb), dim3(EWB), 0, st, dsegs, nb, ws, R,
+    hipLaunchKernelGGL(k_pme_tile_scatter, dim3(xcd_grid(nb * h.bpb)), dim3(EWB), 0, st, dsegs, nb, ws, R,
                        fdsign, fdh);
 }
 

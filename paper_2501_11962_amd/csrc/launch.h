@@ -5,6 +5,9 @@
 
 namespace mop {
 
+// Workgroups to launch for nblk logical blocks taken with xcd_block.
+inline unsigned xcd_grid(int nblk) { return 8u * ((unsigned)(nblk + 7) / 8u); }
+
 // Bin every pair bead (fdsign: 0 = R, +1 / -1 = R -/+ eps d for the FD term); newton3: also
 // clear the slot-order sums of the Newton-3 pair kernels.
 void run_binning(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char* ws,
