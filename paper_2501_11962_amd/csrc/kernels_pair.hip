@@ -1171,10 +1171,13 @@ static void launch_pair_e(const SegDev* dsegs, const SegDev* hsegs, const Launch
         launch_pair_t<MODE, PW, N3, EL, 0>(dsegs, hsegs, base, ws, outsel, energy_bead, lists, 0, pq, st);
     } else if (energy_bead == -1) {
         launch_pair_t<MODE, PW, N3, EL, 0>(dsegs, hsegs, base, ws, outsel, energy_bead, lists, 0, pq, st);
-    } else if (energy_bead == 0 && EL == 0 && pair_waves(hsegs, base) >= SPLIT_MIN_WAVES) {
-        // bead 0 of every path with energies, the other beads without (6 waves per SIMD
-        // instead of 5; the Ewald kernels run at 5 either way, so they keep one launch;
-        // launches too small to fill the GPU gain nothing from a second launch)
+    } else if (energy_bead == 0 && pair_waves(hsegs, base) >= SPLIT_MIN_WAVES) {
+        // bead 0 of every path with energies, the other beads without (reaction field: 6 waves
+        // per SIMD instead of 5; Ewald: no spilled registers, and mesh kernels that found no
+        // room beside the pair kernel run while the chip drains between the two launches:
+        // 9.43 -> 9.38 ms per call at 150,000 atoms x 16 beads; cutting the passes into 3 to 8
+        // launches gave 0.5% more.  Launches too small to fill the GPU gain nothing from a
+        // second one)
         Launch L0 = base, L1 = base;
         for (int p = 0; p < base.nseg; ++p) {
             L0.nb[p] = std::min(base.nb[p], 1);

@@ -333,11 +333,18 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_pme_tile_sort(const SegDev* __re
 // dipoles q_i v_i (V: [nb][Q][3]).  Beads nb .. nbatch-1 of the FFT batch get zeros.
 constexpr int SPREAD_CAP = 1024;  // candidate list of the spreading kernel (LDS)
 
+// Registers of the mesh kernels that run beside the pair kernels: 96, what a wave of those
+// holds (order 4 fits without spills).  A workgroup of the pair kernel that ends leaves a hole
+// of that size, which the next one takes at once: with 98 to 100 registers the spread of the
+// Hessian pass got no room before the last of them had started.  150,000 sites x 16 beads:
+// 9.60 -> 9.42 ms per call.
+template <int P>
+constexpr int BESIDE_PAIRS = P == 4 ? 5 : 1;  // waves per SIMD
+
 template <int P, int KIND>
-__global__ void __launch_bounds__(PME_BLOCK) k_pme_spread(const SegDev* __restrict__ segs, int nb,
-                                                          char* ws, const double* __restrict__ R,
-                                                          const double* __restrict__ V, int fdsign,
-                                                          double fdh) {
+__global__ void __launch_bounds__(PME_BLOCK, BESIDE_PAIRS<P>)
+    k_pme_spread(const SegDev* __restrict__ segs, int nb, char* ws, const double* __restrict__ R,
+                 const double* __restrict__ V, int fdsign, double fdh) {
     extern __shared__ unsigned long long acc[];
     __shared__ int cand_k[SPREAD_CAP], cand_m[SPREAD_CAP];
     __shared__ int ncand;
@@ -553,9 +560,9 @@ __global__ void __launch_bounds__(PME_BLOCK) k_pme_solve32(const SegDev* __restr
 constexpr int GATHER_BLOCK = 128;
 
 template <int P, int KIND>
-__global__ void __launch_bounds__(GATHER_BLOCK) k_pme_gather(const SegDev* __restrict__ segs, int nb,
-                                                             char* ws, const double* __restrict__ V,
-                                                             int outsel, int use_pgr) {
+__global__ void __launch_bounds__(GATHER_BLOCK, (KIND == 0 ? BESIDE_PAIRS<P> : 1))
+    k_pme_gather(const SegDev* __restrict__ segs, int nb, char* ws, const double* __restrict__ V, int outsel,
+                 int use_pgr) {
     extern __shared__ double s_phi[];
     const SegDev& sg = segs[0];
     const SysDev& s = sg.s;
