@@ -98,7 +98,7 @@ template <int MODE>
 constexpr int TAB_COPIES = MODE == 1 ? 1 : 2;
 
 // erfcx(x) = exp(x^2) erfc(x) for 0 <= x <= 6.
-__device__ __forceinline__ float erfcx_poly(float x) {
+__device__ __forceinline__ float erfc_ex2(float x) {
     const float t = __builtin_amdgcn_rcpf(fmaf(0.5f, x, 1.0f));
     float p = -3.256256573e-02f;
     p = fmaf(p, t, 2.505454269e-01f);
@@ -226,7 +226,7 @@ __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const 
             r = r2 * rinv;
             const float bx = P.beta * r;
             const float ex2 = __expf(-bx * bx);
-            const float ecx = erfcx_poly(bx);
+            const float ecx = erfc_ex2(bx);
             D = P.c2b * ex2;
             E = exc ? fmaf(ex2, ecx, -1.0f) : ex2 * ecx;
             const float ge = -fmaf(D, rinv2, E * rinv3);
