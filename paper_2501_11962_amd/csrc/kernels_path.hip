@@ -32,6 +32,12 @@ __device__ __forceinline__ void add_mesh(const SegDev& sg, char* ws, size_t off,
     v[2] += m[2];
 }
 
+// Clusters of bead 1 whose pair energies belong to V_eff: kept beside the sums by k_resid,
+// because finite differences that bin R -/+ eps d leave the columns of that configuration.
+__device__ __forceinline__ int* veff_clusters(const SegDev& sg, char* ws) {
+    return wsp<int>(ws, sg.o_eres + 3 * sizeof(double));
+}
+
 // want_dmax: also the per-bead max |d|^2 (finite-difference step, PME dipole-grid scale).
 __global__ void __launch_bounds__(EWB) k_resid(const SegDev* __restrict__ segs, Launch L,
                                                CallPtrs cp, int want_dmax) {
@@ -86,6 +92,9 @@ __global__ void __launch_bounds__(EWB) k_resid(const SegDev* __restrict__ segs, 
     }
     __syncthreads();
     if (threadIdx.x == 0) {
+        // clusters of bead 1 as long as the binning is that of R
+        if (blk == L.pf[p])
+            *veff_clusters(sg, ws) = wsp<const int>(ws, sg.o_colstart)[s.ncol] / CLUSTER;
         double ses = 0.0, seb = 0.0, smax = 0.0;
         for (int k = 0; k < EWB / 64; ++k) {
             ses += sh[0][k];
@@ -102,11 +111,9 @@ __global__ void __launch_bounds__(EWB) k_resid(const SegDev* __restrict__ segs, 
     }
 }
 
-// Sum of the per-cluster pair-energy partials of bead b (weights applied in the kernel).
-__device__ double pair_energy_of_bead(const SegDev& sg, char* ws, int b, int t0, int stride) {
-    const int ncol = sg.s.ncol;
-    const int nslots = wsp<const int>(ws, sg.o_colstart)[(size_t)b * (ncol + 1) + ncol];
-    const int ncl = nslots / CLUSTER;
+// Sum of the pair-energy partials of the ncl clusters of bead b (weights applied in the
+// kernel).
+__device__ double pair_energy_of_bead(const SegDev& sg, char* ws, int b, int ncl, int t0, int stride) {
     const double* ep = wsp<const double>(ws, sg.o_epart) + (size_t)b * sg.s.cpb;
     double e0 = 0.0, e1 = 0.0;
     int c = t0;
@@ -139,7 +146,7 @@ __device__ __forceinline__ void reduce_veff(const SegDev* __restrict__ segs, con
     double es = 0.0, eb = 0.0;
     for (int k = threadIdx.x; k < nbr * sg.bpb; k += EWB) es += rp[2 * k];
     for (int k = threadIdx.x; k < sg.bpb; k += EWB) eb += rp[2 * k + 1];
-    const double ep = pair_energy_of_bead(sg, ws, 0, threadIdx.x, EWB) +
+    const double ep = pair_energy_of_bead(sg, ws, 0, *veff_clusters(sg, ws), threadIdx.x, EWB) +
                       pme_energy_of_bead(sg, ws, 0, threadIdx.x, EWB);
     const double S_es = block_sum(es, sh);
     const double S_u = block_sum(eb + ep, sh) + (sg.s.elec == 1 ? sg.s.e_const : 0.0);
@@ -266,7 +273,9 @@ __global__ void __launch_bounds__(EWB) k_reduce_beads(const SegDev* __restrict__
     const double* rp = wsp<const double>(cp.ws, sg.o_rpart);
     double eb = 0.0;
     for (int k = threadIdx.x; k < sg.bpb; k += EWB) eb += rp[2 * ((size_t)b * sg.bpb + k) + 1];
-    const double ep = pair_energy_of_bead(sg, cp.ws, b, threadIdx.x, EWB) +
+    const int ncol = sg.s.ncol;
+    const int ncl = wsp<const int>(cp.ws, sg.o_colstart)[(size_t)b * (ncol + 1) + ncol] / CLUSTER;
+    const double ep = pair_energy_of_bead(sg, cp.ws, b, ncl, threadIdx.x, EWB) +
                       pme_energy_of_bead(sg, cp.ws, b, threadIdx.x, EWB);
     const double s = block_sum(eb + ep, sh);
     if (threadIdx.x == 0) cp.Uout[sg.vidx + b] = s + (sg.s.elec == 1 ? sg.s.e_const : 0.0);

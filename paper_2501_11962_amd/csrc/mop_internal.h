@@ -17,7 +17,9 @@
 //     the search, in search order: flag << 31 (the cluster may hold excluded partners)
 //     | cluster index << 8 | 8-bit mask of those atoms; nlc:
 //     their count, which may exceed lcap, then the list is incomplete).
-// Per path: FP64 residuals d^n [(N-1)][Q][3], reduction partials, per-bead max |d|^2.
+// Per path: FP64 residuals d^n [(N-1)][Q][3], reduction partials, per-bead max |d|^2;
+//     eres double [4]: V_eff, U(R^1), the spring energy, and (as an int) the clusters of
+//     bead 1 in the binning of R, whose energy partials V_eff sums.
 // Particle-mesh Ewald (systems with Ewald electrostatics), per pair bead:
 //     ptc   int [ntile]    atoms per grid tile; pts int [ntile + 1] their starts
 //     ptid, ptrk int [Q]   tile and rank of each atom
