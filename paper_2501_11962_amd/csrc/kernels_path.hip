@@ -91,10 +91,10 @@ __global__ void __launch_bounds__(EWB) k_resid(const SegDev* __restrict__ segs, 
         sh[2][threadIdx.x >> 6] = d2max;
     }
     __syncthreads();
+    // beside the sums, by a thread that has no part in them
+    if (blk == L.pf[p] && threadIdx.x == EWB - 1)
+        *veff_clusters(sg, ws) = wsp<const int>(ws, sg.o_colstart)[s.ncol] / CLUSTER;
     if (threadIdx.x == 0) {
-        // clusters of bead 1 as long as the binning is that of R
-        if (blk == L.pf[p])
-            *veff_clusters(sg, ws) = wsp<const int>(ws, sg.o_colstart)[s.ncol] / CLUSTER;
         double ses = 0.0, seb = 0.0, smax = 0.0;
         for (int k = 0; k < EWB / 64; ++k) {
             ses += sh[0][k];
