@@ -179,8 +179,10 @@ __global__ void __launch_bounds__(EWB) k_bin_place(const SegDev* __restrict__ se
     wsp<int>(ws, sg.o_slotof)[(size_t)b * Q + i] = slot;
 }
 
-// Padding slots of each column: position of the column's last atom, PAD_W, DUMMY_KEY.
-__global__ void __launch_bounds__(EWB) k_bin_pad(const SegDev* __restrict__ segs, Launch L, char* ws) {
+// Padding slots of each column: position of the column's last atom, PAD_W, DUMMY_KEY
+// (displaced: its position as binned too).
+__global__ void __launch_bounds__(EWB) k_bin_pad(const SegDev* __restrict__ segs, Launch L, char* ws,
+                                                 int displaced) {
     const int blk = blockIdx.x;
     const int p = find_seg(L, blk);
     const SegDev& sg = segs[p];
@@ -195,16 +197,20 @@ __global__ void __launch_bounds__(EWB) k_bin_pad(const SegDev* __restrict__ segs
     uint4* up = wsp<uint4>(ws, sg.o_upos) + (size_t)b * S;
     int2* um = wsp<int2>(ws, sg.o_umeta) + (size_t)b * S;
     int* og = wsp<int>(ws, sg.o_orig) + (size_t)b * S;
+    uint4* vs = wsp<uint4>(ws, sg.o_vs) + (size_t)b * S;
     const uint4 last = up[base + n - 1];
     for (int k = n; k < pad; ++k) {
         up[base + k] = make_uint4(last.x, last.y, last.z, PAD_W);
         um[base + k] = make_int2(DUMMY_KEY, 0);
         og[base + k] = -1;
+        if (displaced) vs[base + k] = vs[base + n - 1];
     }
 }
 
 // Shared-bin finite differences: the displaced coordinates R^b + fdsign eps_b d^b written
-// into the slots the binning of R gave each atom (no new sort).
+// into the slots the binning of R gave each atom (no new sort).  R's own go to vs, which only
+// exact gradients read otherwise: the pair search takes a cluster's column from them, as a
+// displaced atom may lie in the next one.
 __global__ void __launch_bounds__(EWB) k_bin_displace(const SegDev* __restrict__ segs, Launch L,
                                                       char* ws, const double* __restrict__ R,
                                                       int fdsign, double fdh) {
@@ -224,6 +230,8 @@ __global__ void __launch_bounds__(EWB) k_bin_displace(const SegDev* __restrict__
     wsp<uint4>(ws, sg.o_upos)[(size_t)b * sg.s.S + slot] =
         make_uint4(to_fixed(r[0] + eps * d[0], sg.s.L[0]), to_fixed(r[1] + eps * d[1], sg.s.L[1]),
                    to_fixed(r[2] + eps * d[2], sg.s.L[2]), __float_as_uint(sg.s.qs[i]));
+    wsp<uint4>(ws, sg.o_vs)[(size_t)b * sg.s.S + slot] =
+        make_uint4(to_fixed(r[0], sg.s.L[0]), to_fixed(r[1], sg.s.L[1]), to_fixed(r[2], sg.s.L[2]), 0u);
 }
 
 // Overlap check of a binned configuration: sets ST_OVERLAP in the status word, which leads
@@ -580,7 +588,7 @@ void run_displace(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, 
     Lc.pf[0] = 0;
     for (int p = 0; p < base.nseg; ++p)
         Lc.pf[p + 1] = Lc.pf[p] + (base.nb[p] * hsegs[p].s.ncol + EWB - 1) / EWB;
-    hipLaunchKernelGGL(k_bin_pad, dim3(Lc.pf[base.nseg]), dim3(EWB), 0, st, dsegs, Lc, ws);
+    hipLaunchKernelGGL(k_bin_pad, dim3(Lc.pf[base.nseg]), dim3(EWB), 0, st, dsegs, Lc, ws, 1);
 }
 
 template <int J>
@@ -674,7 +682,7 @@ static void bin_general(const SegDev* dsegs, const SegDev* hsegs, const Launch& 
     hipLaunchKernelGGL(k_bin_colstart, dim3(Lb.pf[base.nseg]), dim3(CSB), 0, st, dsegs, Lb, ws);
     hipLaunchKernelGGL(k_bin_scatter, dim3(xcd_grid(La.pf[base.nseg])), dim3(EWB), 0, st, dsegs, La, ws);
     hipLaunchKernelGGL(k_bin_place, dim3(xcd_grid(La.pf[base.nseg])), dim3(EWB), 0, st, dsegs, La, ws);
-    hipLaunchKernelGGL(k_bin_pad, dim3(Lc.pf[base.nseg]), dim3(EWB), 0, st, dsegs, Lc, ws);
+    hipLaunchKernelGGL(k_bin_pad, dim3(Lc.pf[base.nseg]), dim3(EWB), 0, st, dsegs, Lc, ws, 0);
 }
 
 }  // namespace mop

@@ -454,8 +454,8 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
     // neighbour lists (full-shell kernels): the force pass records the slots that pass
     // the search, the Hessian pass of the same bead replays them
     const int lcap = sg->s.lcap;
-    const bool rec = !N3 && MODE == 0 && lists == 1 && lcap > 0;
-    const bool rpl = !N3 && lists == 2 && lcap > 0;
+    const bool rec = !N3 && MODE == 0 && (lists & LISTS_RECORD) && lcap > 0;
+    const bool rpl = !N3 && (lists & LISTS_REPLAY) && lcap > 0;
     int* __restrict__ nl = nullptr;
     int* __restrict__ nlc = nullptr;
     if (rec || rpl) {
@@ -797,8 +797,9 @@ __device__ __forceinline__ void pair_wave(const SegDev* __restrict__ segs, const
         const float Lx = sg->s.Lf[0], Ly = sg->s.Lf[1];
         const float iLx = sg->s.iL[0], iLy = sg->s.iL[1];
         const float cwx = sg->s.cw[0], cwy = sg->s.cw[1];
-        // the column of the i-cluster (its reference atom's; the whole cluster's)
-        const uint4 ref = upos[c * CLUSTER + 3];
+        // the column of the i-cluster: its reference atom's as it was binned
+        const uint4 ref =
+            (MODE == 0 && (lists & KEPT_BINS) ? reinterpret_cast<const uint4*>(vs) : upos)[c * CLUSTER + 3];
         const int cx = fixed_bin(ref.x, ncx), cy = fixed_bin(ref.y, ncy);
         if (k < nst) {
             // stencil half widths are below the column counts (else the stencil spans
@@ -1213,8 +1214,9 @@ void run_pair(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char
         return;
     }
     if (newton3) {
-        if (mode == 0) launch_pair_w<0, 1, 0>(dsegs, hsegs, base, ws, outsel, energy_bead, waves, 0, st);
-        else launch_pair_w<1, 1, 0>(dsegs, hsegs, base, ws, outsel, energy_bead, waves, 0, st);
+        lists &= KEPT_BINS;
+        if (mode == 0) launch_pair_w<0, 1, 0>(dsegs, hsegs, base, ws, outsel, energy_bead, waves, lists, st);
+        else launch_pair_w<1, 1, 0>(dsegs, hsegs, base, ws, outsel, energy_bead, waves, lists, st);
         Launch L = base;
         L.pf[0] = 0;
         for (int p = 0; p < base.nseg; ++p) L.pf[p + 1] = L.pf[p] + base.nb[p] * hsegs[p].bpb;

@@ -354,8 +354,10 @@ static SysDev plan_geometry(const mop_system_s* sys, const mop_plan_opts* opts) 
     if (s.ally) s.wy = s.ncy;
     // Columns of the square stencil that no atom of the centre column can reach (corners) are
     // left out when the rest fits one column per lane: 61 of 81 for a 1.2 nm cutoff and 0.4
-    // nm columns, one pass of the search's column step instead of two.  The 0.001 nm more
-    // than cover what displacements of a kept binning and rounding could add.
+    // nm columns, one pass of the search's column step instead of two.  Where displaced atoms
+    // keep the binning of R, both atoms of a pair may lie up to fd_h (1e-4 nm, for which
+    // that is exact) outside their columns, which the search margin covers; the 0.001 nm more
+    // are for rounding of the column faces.
     s.nst = 0;
     if (!s.allx && !s.ally && s.rx < 128 && s.ry < 128) {
         int n = 0;
@@ -1016,8 +1018,8 @@ static void path_sequence(const SegDev* dsegs, const SegDev* hsegs, const Launch
     mark(1);
     // exact gradients: the force pass records neighbour lists for the Hessian pass; with
     // shared-bin finite differences, for the two displaced force passes
-    const int lists = (grad && (mode == 0 || mode == 2)) ? 1 : 0;
-    run_pair(dsegs, hsegs, base, cp.ws, 0, 0, 0, waves, n3, st, lists);
+    const bool lists = grad && (mode == 0 || mode == 2);
+    run_pair(dsegs, hsegs, base, cp.ws, 0, 0, 0, waves, n3, st, lists ? LISTS_RECORD : 0);
     mark(2);
     if (side) join_side(pl, st);
     else if (pme) pme_forces(pl, base.nb[0], cp, 0, 3, true, st);
@@ -1039,7 +1041,7 @@ static void path_sequence(const SegDev* dsegs, const SegDev* hsegs, const Launch
             fork_side(pl, st);
             pme_hvp(pl, Lh.nb[0], cp, d64, pl->side);
         }
-        if (any && mode == 0) run_pair(dsegs, hsegs, Lh, cp.ws, 1, 0, -1, waves, n3, st, 2 * lists);
+        if (any && mode == 0) run_pair(dsegs, hsegs, Lh, cp.ws, 1, 0, -1, waves, n3, st, LISTS_REPLAY);
         mark(5);
         if (mesh && side) join_side(pl, st);
         else if (mesh) pme_hvp(pl, Lh.nb[0], cp, d64, st);
@@ -1050,7 +1052,7 @@ static void path_sequence(const SegDev* dsegs, const SegDev* hsegs, const Launch
                 if (mode == 1) run_binning(dsegs, hsegs, Lh, cp.ws, cp.R, sgn, cp.fd_h, n3, st);
                 else run_displace(dsegs, hsegs, Lh, cp.ws, cp.R, sgn, cp.fd_h, st);
                 run_pair(dsegs, hsegs, Lh, cp.ws, 0, sgn > 0 ? 1 : 2, -1, waves, n3, st,
-                         mode == 2 ? 2 * lists : 0);
+                         mode == 2 ? LISTS_REPLAY | KEPT_BINS : 0);
                 if (pme) pme_forces(pl, Lh.nb[0], cp, sgn, sgn > 0 ? 1 : 2, true, st);
             }
         }

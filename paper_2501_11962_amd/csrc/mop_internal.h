@@ -9,7 +9,8 @@
 //                  in padding slots}
 //     umeta int2   {16 * exclusion key + LJ type, LJ type}
 //     orig  int    atom index of the slot (-1 for padding)
-//     vs    float4 the vector of a Hessian-vector product and the packed key, slot order
+//     vs    float4 the vector of a Hessian-vector product and the packed key, slot order; in
+//                  displaced passes on the binning of R: uint4, R's fixed-point coordinates
 //     fs    float  x3 pair sums in slot order (structure of arrays), Newton-3 kernels
 //   Per atom (original order): slotof, pair force / pair HVP outputs (float4).
 //   Per cluster: the neighbour list a force pass records for the Hessian pass of the
@@ -53,6 +54,10 @@ constexpr int EWB = 256;          // block size of the elementwise kernels
 constexpr int WAVES_PERSISTENT = 0x100;  // or-ed into a plan's waves: persistent pair launches
 constexpr size_t WS_QUEUE = 64;   // workspace byte offset of the 8 work-queue counters
 constexpr int32_t DUMMY_KEY = INT32_MIN;
+// What a pair pass does with the neighbour lists and the binning (bits).
+constexpr int LISTS_RECORD = 1;   // force pass: write the lists
+constexpr int LISTS_REPLAY = 2;   // read the lists of an earlier pass over the same binning
+constexpr int KEPT_BINS = 4;      // force pass: the atoms have moved since they were binned
 constexpr uint32_t PAD_W = 0xFFFFFFFFu;  // upos.w of a padding slot (a NaN: no charge)
 
 // Status bits (mirrors MOP_DEV_* of the public header).

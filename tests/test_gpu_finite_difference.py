@@ -1,9 +1,11 @@
 """Finite-difference gradients where the displacement carries an atom over a face of its
-column: V_eff belongs to R whatever the binning of R - eps d looks like (mode 1).
+column: V_eff belongs to R whatever the binning of R - eps d looks like (mode 1), and the
+search on the binning of R finds every pair of the displaced atoms (mode 2).
 
-The systems are charged Lennard-Jones lattices without bonds, with an atom set 0.4e-4 nm from
-a column face and moving across it (a path of two beads whose increment is 0.05 nm for that
-atom, so that the largest displacement is fd_h = 1e-4 nm, and zero for the others).
+The systems are charged Lennard-Jones lattices without bonds, with one or a few atoms set
+0.4e-4 nm from a column face and moving across it (a path of two beads whose increment is
+0.05 nm for those atoms, so that the largest displacement is fd_h = 1e-4 nm, and zero for the
+others).
 """
 import numpy as np
 import pytest
@@ -35,6 +37,10 @@ def ctx(mop):
 def cuda(x):
     import torch
     return torch.from_numpy(np.ascontiguousarray(x, np.float64)).cuda()
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
 
 
 def lattice(Q, seed, rc, box=1.97, m=7):
@@ -118,3 +124,58 @@ def test_veff_of_rebinned_finite_differences_is_that_of_the_path(grow, pme, mop,
         _, vb = bt.veff_grad(bt.pack([cuda(R), cuda(R[:1])]), mode=1, fd_h=FD_H)
         assert bt.status() == 0
         assert float(vb[0]) == v0
+
+
+def path_with_straying_references(info, s, seed):
+    """A path of two beads in which the fourth atom of as many clusters as possible lies just
+    inside an x or y face of its column and is moved across it by +eps d or by -eps d.  (The
+    search takes a cluster's fourth slot as its reference.)"""
+    rng = np.random.default_rng(seed)
+    x = s["x"].copy()
+    n = [info["ncx"], info["ncy"]]
+    col = columns(s, info, x)
+    zb = bins(x[:, 2], s["box"][2], info["nzb"])
+    out = np.zeros(x.shape)
+    moved = 0
+    for c in np.unique(col):
+        atoms = np.nonzero(col == c)[0]
+        atoms = atoms[np.lexsort((atoms, zb[atoms]))]     # slot order
+        for i in atoms[3::8]:
+            a, up = int(rng.integers(2)), bool(rng.integers(2))
+            w = s["box"][a] / n[a]
+            k = (c // n[1]) if a == 0 else (c % n[1])
+            y = x.copy()
+            y[i, a] = (k + 1) * w - NEAR if up else k * w + NEAR
+            if clear_of(y, i, s["box"]):
+                x, moved = y, moved + 1
+                out[i, a] = STEP * rng.choice([-1.0, 1.0])
+    assert np.array_equal(columns(s, info, x), col) and moved >= 10
+    return np.stack([x, x + out])
+
+
+# columns of about rc / 1.9: the outermost column of the stencil starts at half the cut-off
+@pytest.mark.parametrize("pme", [False, True])
+@pytest.mark.parametrize("how", [dict(newton3=True), dict(list_cap=-1), dict(list_cap=1), dict()])
+def test_kept_binning_finds_every_pair_of_displaced_atoms(how, pme, mop, ctx):
+    """Finite differences on the binning of R against re-binned ones: searched (Newton-3
+    kernels, no lists, lists that overflow) and replayed.  eps is 2e-3, so the FP32 forces (1e3,
+    to 1e-7) leave 1e-2 per component beside a gradient of 1e5: 1e-7, held to 1e-5.  A missed
+    pair is wrong by its whole force / (4 eps)."""
+    if pme and how.get("newton3"):
+        pytest.skip("Newton-3 kernels are for reaction field")
+    s = lattice(256, 3, 0.6)
+    if pme:
+        s = W.with_pme(s)
+    sysm = mop.System(ctx, s)
+    plan = mop.Plan(sysm, 2, col_width=0.6 / 1.9, **how)
+    info = plan.info()
+    assert info["ncx"] == 6 and info["ncy"] == 6
+    R = path_with_straying_references(info, s, 4)
+    G2, v2 = mop.veff_grad(plan, cuda(R), mode=2, fd_h=FD_H)
+    ref = mop.Plan(sysm, 2)
+    G1, v1 = mop.veff_grad(ref, cuda(R), mode=1, fd_h=FD_H)
+    assert plan.status() == 0 and ref.status() == 0
+    e = rel(G2.cpu().numpy(), G1.cpu().numpy())
+    print(f"[fd kept bins] {how} pme={pme}: G {e:.2e}", flush=True)
+    assert e < 1e-5
+    assert abs(float(v2[0]) - float(v1[0])) < 1e-6 * abs(float(v1[0]))
