@@ -121,8 +121,8 @@ constexpr int SLOTS = 128;  // power of two, at least 63 + 64
 constexpr int XMAP = 128;   // words (XSKIP kernels)
 // The flag of such a cluster: bit 23 of its index in the candidate list, which makes it bit
 // 26 of a listed slot and bit 31 of a neighbour-list record.  Layouts of 2^26 slots or more
-// have no room for it (and no lists), and repeated keys no map to the atoms; there every
-// batch is tested.
+// have no room for it (and no lists), and keys that repeat or leave wide gaps no map to the
+// atoms; there every batch is tested.
 constexpr int XFLAG = 1 << 23;
 constexpr int XSLOT = XFLAG * CLUSTER;
 template <class F>

@@ -639,14 +639,22 @@ int mop_system_create(mop_ctx ctx, const mop_system_desc* d, mop_system* out) {
     s.nbond_entries = 2 * d->nbonds;
     int e = 0;
     if (!e) e = upload(sys, qs.data(), Q, &s.qs);
-    std::vector<int> kmap(*std::max_element(key.begin(), key.end()) + 1, -1);
-    bool one_each = true;  // explicit positions may repeat inside a molecule
-    for (int i = 0; i < Q; ++i) {
-        one_each = one_each && kmap[key[i]] < 0;
-        kmap[key[i]] = i;
+    // Map from keys to atoms, for the Ewald kernels' marks of clusters with excluded partners.
+    // Keys of bonded chains and of positions without gaps are below 3 Q; explicit positions may
+    // leave gaps (keys up to 2^27) or repeat inside a molecule, and then there is none.
+    std::vector<int> kmap;
+    if (s.elec == 1) {
+        const int top = *std::max_element(key.begin(), key.end());
+        if (top < 4LL * Q) {
+            kmap.assign(top + 1, -1);
+            for (int i = 0; i < Q && !kmap.empty(); ++i) {
+                if (kmap[key[i]] >= 0) kmap.clear();
+                else kmap[key[i]] = i;
+            }
+        }
     }
-    s.nkey = one_each ? (int)kmap.size() : 0;
-    if (!e) e = upload(sys, kmap.data(), kmap.size(), &s.kmap);
+    s.nkey = (int)kmap.size();
+    if (!e && s.nkey > 0) e = upload(sys, kmap.data(), kmap.size(), &s.kmap);
     for (int i = 0; i < Q; ++i) key[i] = key[i] * 16 + typ[i];  // type < MAXTYPES = 16
     if (!e) e = upload(sys, key.data(), Q, &s.key);
     if (!e) e = upload(sys, typ.data(), Q, &s.type);

@@ -99,7 +99,7 @@ struct SysDev {
     const int* key;       // [Q] 16 * exclusion key + LJ type; excluded pairs: |key_i - key_j| <= 2
     const int* type;      // [Q]
     const int* kmap;      // [nkey] atom of an exclusion key, -1: none
-    int nkey;             // 0: keys repeat, no such map
+    int nkey;             // 0: no such map (reaction field; keys that repeat or leave gaps)
     const double* c;      // [Q] dt / (m nu)
     const double* K;      // [Q] m nu / (2 dt)
     const double* minv;   // [Q] 1 / m (path dynamics)
