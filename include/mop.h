@@ -206,6 +206,7 @@ int mop_workspace_size(mop_plan plan, size_t* bytes);
  * Physical forces of B independent configurations (the do_force call of section 2.1):
  *   R  [B][Q][3] double in;   F [B][Q][3] float out, F = -grad U(R^b)
  *   U  [B] double out (potential energy per configuration) or NULL
+ * Reaction-field forces with and without energies may differ in their last FP32 bits.
  */
 int bead_forces(mop_plan plan, const double* R, int32_t B, float* F, double* U, void* ws);
 

@@ -171,10 +171,16 @@ constexpr bool THREE_Q = MODE == 1 && N3 == 0 && EL == 0;
 // the 150,000-atom workload): no selects on the results, and the idle lanes draw no
 // power, which the kernels are short of (they run at 1.8-2.1 GHz of the GPU's 2.4).
 // Every fused multiply-add is written out (contraction is off), so that the variants of
-// the kernels agree bit for bit.
+// the kernels round alike, but for cube_first.
 // toff: byte offset of type j in the table row (XSKIP kernels; the others take the type
 // from kj); EXCL: the pair may be excluded (kj is read).
-// cube_first: r^-3 is rounded before it is taken from 2 k_rf (force, reaction field).
+// cube_first (force, reaction field; the first step of a full batch in kernels with
+// energies): r^-3 is rounded before it is taken from 2 k_rf.  It gains nothing: so the
+// compiler formed that step when it chose the fused operations itself, and trajectories and
+// gradients of earlier builds are reproduced only with it (without, gradients move by 3e-9 to
+// 4e-8, their error against 64 bits by nothing).  Forces of a kernel with energies differ in
+// the last bits from those of one without: bead_forces with and without energies, and a
+// path's beads after the first when its launch is large enough to be split (launch_pair_e).
 template <int MODE, bool EX, bool WANTE, bool T_OUT, int EL, bool Q3, bool EXCL>
 __device__ __forceinline__ void pair_term(const IAtom& I, const PairK& P, const float4* tabrow,
                                           int ntab,
