@@ -9,6 +9,7 @@
 // HBM-bound, O(Q) per bead.
 #include <algorithm>
 
+#include "bin_forms.h"
 #include "device_common.h"
 #include "launch.h"
 
@@ -622,20 +623,18 @@ static void launch_overlap(const SegDev* dsegs, const SegDev* hsegs, const Launc
 
 void run_binning(const SegDev* dsegs, const SegDev* hsegs, const Launch& base, char* ws,
                  const double* R, int fdsign, double fdh, int newton3, hipStream_t st) {
-    // One workgroup per bead (k_bin_bead) or eight kernels over all beads.  With its atoms
-    // in registers the first is faster for any number of beads: 24 against 47 us for 64
-    // beads of 3,000 atoms, 10 against 25 for one of 256.  Beyond, a workgroup takes about
-    // 12 us + 3.4 ns per atom whatever the number of beads, the eight kernels 28 us +
-    // 0.086 ns per atom and bead (measured from 5,000 x 1 to 30,000 x 32; 140 against 221
-    // us for 96 beads of 22,999), which cross at atoms x (40 - beads) = 186,000.
+    // one workgroup per bead (k_bin_bead) or eight kernels over all beads
+    BinPath path[MAXSEG];
+    for (int p = 0; p < base.nseg; ++p) {
+        const SysDev& s = hsegs[p].s;
+        path[p] = {s.Q, base.nb[p], fused_regs(s), fused_any(s), 0};
+    }
+    choose_bin_forms(path, base.nseg);
     char which[MAXSEG] = {};
     Launch G = base, O = base;  // beads binned by the eight kernels / with the overlap check apart
     bool rest = false, one = false, two = false;
-    long long beads = 0;
-    for (int p = 0; p < base.nseg; ++p) beads += base.nb[p];
     for (int p = 0; p < base.nseg; ++p) {
-        const SysDev& s = hsegs[p].s;
-        which[p] = fused_regs(s) ? 1 : fused_any(s) && s.Q * (40 - beads) <= 186000 ? 2 : 0;
+        which[p] = (char)path[p].form;
         if (which[p]) G.nb[p] = 0;
         if (which[p] == 1) O.nb[p] = 0;
         one = one || which[p] == 1;
