@@ -558,22 +558,30 @@ __global__ void __launch_bounds__(PME_BLOCK) k_pme_solve32(const SegDev* __restr
 // gradient call 10.3 -> 9.8 ms; 3000 sites x 16 beads, where filling the tile takes longest:
 // 8.4 -> 10.9 and 12.9 -> 14.8 us beside the pair kernels, which end later (call unchanged).
 constexpr int GATHER_BLOCK = 128;
+// Tiles with more atoms on average are shared by several workgroups (parts), each of which
+// fills the tile and takes every parts-th run of 128.  With the grid of the default spacing a
+// tile has about 100 atoms; on coarser grids, with one workgroup per tile, that was a serial
+// chain: 3000 sites x 16 beads on 14^3 points (one tile) 391 us a gradient, 30000 x 4 2590;
+// in parts 288 and 1517 (from the L1 291 and 1490).  Parts of 128, 512 and 1024: 286, 295, 315
+// and 1520, 1524, 1545; 30000 x 16 1736, 1692, 1692 and with 256 1707.
+constexpr int GATHER_ATOMS = 256;
 
 template <int P, int KIND>
 __global__ void __launch_bounds__(GATHER_BLOCK, (KIND == 0 ? BESIDE_PAIRS<P> : 1))
     k_pme_gather(const SegDev* __restrict__ segs, int nb, char* ws, const double* __restrict__ V, int outsel,
-                 int use_pgr) {
+                 int use_pgr, int parts) {
     extern __shared__ double s_phi[];
     const SegDev& sg = segs[0];
     const SysDev& s = sg.s;
-    const int blk = xcd_block(nb * s.ntile);
+    const int blk = xcd_block(nb * s.ntile * parts);
     if (blk < 0) return;
-    const int b = blk / s.ntile;
-    const int t = blk - b * s.ntile;
+    const int bt = blk / parts;
+    const int b = bt / s.ntile;
+    const int t = bt - b * s.ntile;
     if (b >= nb) return;
     const int* start = wsp<const int>(ws, sg.o_pts) + (size_t)b * (s.ntile + 1) + t;
-    const int a0 = start[0], a1 = start[1];
-    if (a0 == a1) return;
+    const int a0 = start[0] + (blk - bt * parts) * GATHER_BLOCK, a1 = start[1];
+    if (a0 >= a1) return;
     const int t2 = t % s.ntl[2], t1 = (t / s.ntl[2]) % s.ntl[1], t0 = t / (s.ntl[2] * s.ntl[1]);
     const int tt[3] = {t0, t1, t2};
     int lo[3], n[3];  // first point held (tile minus P - 1) and points held per axis
@@ -614,7 +622,7 @@ __global__ void __launch_bounds__(GATHER_BLOCK, (KIND == 0 ? BESIDE_PAIRS<P> : 1
         }
     }
     __syncthreads();
-    for (int slot = a0 + (int)threadIdx.x; slot < a1; slot += GATHER_BLOCK) {
+    for (int slot = a0 + (int)threadIdx.x; slot < a1; slot += parts * GATHER_BLOCK) {
         const int4 ab = wsp<const int4>(ws, sg.o_ptb)[(size_t)b * s.Q + slot];
         const double4 aw = wsp<const double4>(ws, sg.o_ptw)[(size_t)b * s.Q + slot];
         const int i = ab.w;
@@ -741,15 +749,16 @@ void spread_p(const SegDev* dsegs, const SegDev& h, int nb, int nbatch, char* ws
 template <int P>
 void gather_p(const SegDev* dsegs, const SegDev& h, int nb, char* ws, const double* V, int kind,
               int outsel, int use_pgr, hipStream_t st) {
-    const dim3 grid(xcd_grid(nb * h.s.ntile));
+    const int parts = (h.s.Q - 1) / (h.s.ntile * GATHER_ATOMS) + 1;
+    const dim3 grid(xcd_grid(nb * h.s.ntile * parts));
     size_t pts = 1;
     for (int a = 0; a < 3; ++a) pts *= (size_t)h.s.tile_max[a] + P - 1;
     if (kind == 0)
         hipLaunchKernelGGL((k_pme_gather<P, 0>), grid, dim3(GATHER_BLOCK), pts * 8, st, dsegs, nb, ws, V,
-                           outsel, use_pgr);
+                           outsel, use_pgr, parts);
     else
         hipLaunchKernelGGL((k_pme_gather<P, 1>), grid, dim3(GATHER_BLOCK), pts * 12, st, dsegs, nb, ws, V,
-                           outsel, use_pgr);
+                           outsel, use_pgr, parts);
 }
 
 }  // namespace
