@@ -247,6 +247,10 @@ __global__ void __launch_bounds__(EWB) k_bin_displace(const SegDev* __restrict__
 // Looking through the bins around every atom instead (two columns per axis, bin bounds
 // read first) took 61 us for 15 beads of 150,000 atoms and 17 of the 28 us of the
 // one-workgroup binning of 3,000.
+// Past 16 partners a thread stops at its first hit: the status has no more to say, and where a
+// run has diverged (coordinates that are not finite share one bin) every pair would be tested,
+// one after another: 5,349 atoms x 2 beads 2506 us a gradient, now 806; 3,000 x 2, where
+// k_bin_bead does the same, 1834 and 968.
 // pos(slot) and key(slot) read a slot; first(col, zb) and end(col, zb) give a bin's slots.
 template <class Pos, class Key, class First, class End>
 __device__ __forceinline__ bool overlaps(const SysDev& s, int si, uint32_t ux, uint32_t uy, uint32_t uz,
@@ -265,13 +269,21 @@ __device__ __forceinline__ bool overlaps(const SysDev& s, int si, uint32_t ux, u
     // upper end of the z bins to look through; all of them after a wrap (d < box height)
     const uint32_t zt = uz + d2;
     const int zb1 = zt < uz ? nzb - 1 : fixed_bin(zt, nzb);
-    for (int sj = si + 1; sj < nslots; ++sj) {
-        const uint4 uj = pos(sj);
-        if (uj.w == PAD_W || fixed_bin(uj.z, nzb) > zb1 || fixed_bin(uj.x, ncx) != cx ||
-            fixed_bin(uj.y, ncy) != cy)
-            break;
-        test(sj, uj);
-    }
+    int sj = si + 1;
+    auto column = [&](int end, bool first_hit) __attribute__((always_inline)) {
+        for (; sj < end && !(first_hit && hit); ++sj) {
+            const uint4 uj = pos(sj);
+            if (uj.w == PAD_W || fixed_bin(uj.z, nzb) > zb1 || fixed_bin(uj.x, ncx) != cx ||
+                fixed_bin(uj.y, ncy) != cy)
+                return;
+            test(sj, uj);
+        }
+    };
+    // the few partners of most atoms without a look at what was found (35 against 42 us at
+    // 150,000 atoms x 15 beads)
+    const int few = min(nslots, si + 17);
+    column(few, false);
+    if (sj == few) column(nslots, true);
     auto bins = [&](int col, int za, int zb) __attribute__((always_inline)) {  // za .. zb, wrapping
         for (int z = za;; z = z + 1 == nzb ? 0 : z + 1) {
             const int e = end(col, z);
@@ -501,12 +513,16 @@ __global__ void __launch_bounds__(FB) k_bin_bead(const SegDev* __restrict__ segs
         const int off = s_bin[col * nzb + zb];
         const int n = (zb + 1 < nzb ? s_bin[col * nzb + zb + 1] : s_cnt[col]) - off;
         const int first = s_start[col] + off;
-        int r = 0;
-        for (int k = 0; k < n; ++k) {
-            const int o = s_tmp[first + k];
-            r += o < i;
-            if (REGS && o > i) near(i, v, o);
-        }
+        int r = 0, k = 0;
+        auto ranks = [&](int end, bool first_hit) __attribute__((always_inline)) {
+            for (; k < end; ++k) {
+                const int o = s_tmp[first + k];
+                r += o < i;
+                if (REGS && o > i && !(first_hit && hit)) near(i, v, o);
+            }
+        };
+        ranks(min(n, 16), false);  // as in overlaps()
+        ranks(n, true);
         const int slot = first + r;
         upos[slot] = make_uint4(v.x, v.y, v.z, __float_as_uint(sg.s.qs[i]));
         umeta[slot] = make_int2(sg.s.key[i], sg.s.type[i]);
@@ -558,7 +574,7 @@ __global__ void __launch_bounds__(FB) k_bin_bead(const SegDev* __restrict__ segs
     }
     __syncthreads();
     if (REGS) {
-        for (int t = tid; t < min(s_ntask, TASKS); t += FB) {
+        for (int t = tid; t < min(s_ntask, TASKS) && !hit; t += FB) {
             const int i = (int)(s_task[t] >> 16);
             scan_bin(i, make_uint4(s_x[i], s_y[i], s_z[i], 0u), (int)(s_task[t] & 0xFFFFu));
         }

@@ -115,3 +115,27 @@ def test_overlaps_beyond_the_task_list(mop, ctx):
             mop.bead_forces(plan, cuda(R2))
             assert plan.status() == want, (i, d)
     plan.clear_status()
+
+
+@pytest.mark.parametrize("Q", [3000, 6000])
+def test_overlaps_in_crowded_bins(Q, mop, ctx):
+    """Bins of 1 nm hold a hundred atoms; a pair 0.006 nm apart whose slots lie far from each
+    other in one bin is found, and none at 0.05 nm (registers and the separate check)."""
+    s = W.water_box(Q, 48, rc=0.6)
+    R, _, _ = W.random_walk_path(s, 2, 49, 0.0)
+    plan = mop.Plan(mop.System(ctx, s), 2, col_width=1.0, zbin=1.0)
+    info = plan.info()
+    assert Q / (info["ncx"] * info["ncy"] * info["nzb"]) > 80
+    at = (0.5 / np.array([info["ncx"], info["ncy"], info["nzb"]])) * s["box"]   # centre of a bin
+    for i, j in ((1, 4), (1, Q - 2), (Q // 2, Q - 5), (Q - 8, 7)):
+        for d, want in ((0.006, mop.MOP_DEV_OVERLAP), (0.05, 0)):
+            R2 = R.copy()
+            # nothing else near: the other sites of the bin's centre move half a box away
+            c = R2[1] - at
+            c -= s["box"] * np.rint(c / s["box"])
+            R2[1][(c ** 2).sum(1) < 0.09 ** 2] += 0.5 * s["box"]
+            R2[1, i], R2[1, j] = at, at + [0.0, d, 0.0]
+            plan.clear_status()
+            mop.bead_forces(plan, cuda(R2))
+            assert plan.status() == want, (i, j, d)
+    plan.clear_status()
