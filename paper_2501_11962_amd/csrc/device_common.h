@@ -16,10 +16,13 @@ __device__ __forceinline__ int find_seg(const Launch& L, int blk) {
 // Logical block of this workgroup among nblk (launch xcd_grid(nblk) of them), or -1.
 // Workgroups are dealt to the 8 XCDs in turn; each XCD takes an eighth of the logical order,
 // about its share of whole beads.  Kernels that scatter to or gather from a bead's arrays
-// then work in one L2, where the partial lines written by neighbouring blocks meet.  150,000
-// atoms x 16 beads: residuals 121 -> 93 us, placing 96 -> 84, reserving 22 -> 15, overlap check
-// 70 -> 64, tile scatter 96 -> 83, the gradient call 5.26 -> 5.18 ms.  Counting into bins (86 ->
-// 92 us: its atomics meet in one L2) and the mesh spread (411 -> 434) keep the plain order.
+// then work in one L2, where the partial lines written by neighbouring blocks meet.  How much
+// that gives depends on the order of the atoms.  150,000 atoms x 16 beads, plain -> XCD order,
+// for the relaxed membrane of the benchmark and for that of the performance cases: residuals
+// 100 -> 87 and 100 -> 88 us, placing 51 -> 35 and 78 -> 62, reserving 18 -> 13 and 22 -> 15,
+// overlap check 40 -> 37 and 55 -> 52, tile scatter 39 -> 33 and 95 -> 83, tile count 49 -> 59
+// and 93 -> 85, gathers 113 -> 110 and 184 -> 179.  Counting into bins (86 -> 92 us: its atomics
+// meet in one L2) and the mesh spread (411 -> 434) keep the plain order.
 __device__ __forceinline__ int xcd_block(int nblk) {
     const int per = (nblk + 7) >> 3;
     const int blk = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);

@@ -3,7 +3,7 @@
 // and B (section 3: ligand and binding pocket), and a Gaussian bias V(S) on it.
 //
 // One block per call (the groups are small), bound by the latency of its steps: each wave
-// sums a sixteenth of the atoms of one (bead, group) pair, so that all moments meet at one
+// sums a quarter of the atoms of one (bead, group) pair, so that all moments meet at one
 // barrier and the Gaussians at a second (block-wide sums one after another, two barriers
 // each, took 17 us for groups of 8 and 187 atoms).
 //   1. centres of mass of A and B in beads 1 and N, each from the minimum-image offsets to

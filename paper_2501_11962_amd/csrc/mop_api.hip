@@ -199,9 +199,9 @@ static double ewald_beta(double rc, double rtol) {
 
 // Exclusion key per atom: the molecule's offset plus the position along its chain.
 // Molecules get offsets in the order of their ids, each one its largest position + 3
-// after the previous one, so |key_i - key_j| <= 2 only within a molecule and every key is
-// below Q + 3 * (number of molecules) <= 4 Q.  Keys must stay below 2^27: the pair kernels
-// keep key * 16 + LJ type in one 32-bit word.
+// after the previous one, so |key_i - key_j| <= 2 only within a molecule, and where positions
+// leave no gaps every key is below Q + 2 * (number of molecules) <= 3 Q.  Keys must stay below
+// 2^27: the pair kernels keep key * 16 + LJ type in one 32-bit word.
 // Without explicit molecules the bonds must form linear chains (degree <= 2, no cycles),
 // which are walked from one end.
 static int make_keys(const mop_system_desc* d, std::vector<int>& key) {
